@@ -1,19 +1,24 @@
 // C-ABI of the surrogate MLP: parameters, forward with input gradient,
 // full gradients and the Adam training step.  Kernels in mlp_kernels.h.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <vector>
 
 #include "internal.h"
 #include "mlp_fused.h"
-#include "mlp_kernels.h"
+#include "mlp_train.h"
 
 namespace pcsdf {
 
-constexpr int kChunk = 1024;  // rows per weight-gradient chunk
-// 32-row blocks per wave in fused inference: 2 fits two workgroups per CU
-// (70 KB of LDS each), 4 halves the weight reads per row.
-constexpr int kInferRowBlocks = 2;
+// Rows per partial of the weight gradient: at most kMaxParts partials
+// while each covers at most kChunk rows (65,536 rows: 128 partials of 512
+// rows, so that the 128 x 5 workgroups fill the chip and the partials, 216
+// KB each, stay a fifth of the bytes the kernel reads).
+constexpr int kChunk = 1024, kMaxParts = 128;
+// Row tiles of the fused inference in flight at once: two workgroups per
+// CU on 256 CUs.
+constexpr int kInferBlocks = 512;
 constexpr int kWofs[5] = {0, 4096, 20480, 36864, 53248};
 constexpr int kWbfTotal = 53376;
 
@@ -26,37 +31,37 @@ struct Mlp {
   int64_t step = 0;  // Adam steps taken
   // workspace, grown with the batch
   int cap = 0;
-  DevBuf a0, act, dact, dz, seed, y, wpart, bpart, lpart;
+  DevBuf a0, act, dz, seed, wpart, lpart;
 };
+
+static int chunk_rows(int npad) {
+  const int r = (npad + kMaxParts - 1) / kMaxParts;
+  return std::min(kChunk, (r + kSlabRows - 1) / kSlabRows * kSlabRows);
+}
+static int chunk_count(int npad) {
+  const int r = chunk_rows(npad);
+  return (npad + r - 1) / r;
+}
 
 static int ws(Mlp *m, int npad, hipStream_t s) {
   Handle *h = m->h;
   if (npad <= m->cap) return PCSDF_OK;
   const size_t r = (size_t)npad;
+  // a smaller batch may use more, shorter chunks, but never more than
+  // kMaxParts where a larger one does not
+  const size_t parts = std::max(chunk_count(npad), std::min(kMaxParts, npad / kSlabRows));
   int rc;
   if ((rc = ensure_buffer(h, m->a0, r * kInPad * 2, s)) ||
       (rc = ensure_buffer(h, m->act, 4 * r * kHid * 2, s)) ||
-      (rc = ensure_buffer(h, m->dact, 4 * r * kHid * 2, s)) ||
       (rc = ensure_buffer(h, m->dz, 4 * r * kHid * 2, s)) ||
       (rc = ensure_buffer(h, m->seed, r * 4, s)) ||
-      (rc = ensure_buffer(h, m->y, r * 4, s)) ||
-      (rc = ensure_buffer(h, m->wpart, (r / kChunk) * kHid * kHid * 4, s)) ||
-      (rc = ensure_buffer(h, m->bpart, (r / kChunk) * (kHid + 1) * 4, s)) ||
-      (rc = ensure_buffer(h, m->lpart, (r / 256 + 1) * 4, s)))
+      (rc = ensure_buffer(h, m->wpart, parts * kPartLen * 4, s)) ||
+      (rc = ensure_buffer(h, m->lpart, r / 32 * 4, s)))
     return rc;
   m->cap = npad;
   return PCSDF_OK;
 }
 
-static uint16_t *actp(Mlp *m, int l) {  // A_l, l = 1..4, [cap][128]
-  return reinterpret_cast<uint16_t *>(m->act.ptr) + (size_t)(l - 1) * m->cap * kHid;
-}
-static uint16_t *dp(Mlp *m, int l) {  // D_l, l = 0..3
-  return reinterpret_cast<uint16_t *>(m->dact.ptr) + (size_t)l * m->cap * kHid;
-}
-static uint16_t *dzp(Mlp *m, int l) {  // dZ_l, l = 0..3
-  return reinterpret_cast<uint16_t *>(m->dz.ptr) + (size_t)l * m->cap * kHid;
-}
 static const uint16_t *wb(Mlp *m, int l) {
   return reinterpret_cast<const uint16_t *>(m->wbf.ptr) + kWofs[l];
 }
@@ -72,114 +77,41 @@ static unsigned blocks(int64_t n, int per) {
   return (unsigned)((n + per - 1) / per);
 }
 
-// Sums the chunk partials of one layer's weight gradient into the flat
-// gradient vector: W [out][in] from part [chunks][out][in_pad].
-__global__ __launch_bounds__(256) void k_sum_w(const float *__restrict__ part,
-                                               int chunks, int out, int in,
-                                               int in_pad,
-                                               float *__restrict__ g) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  if (t >= out * in) return;
-  const int o = t / in, i = t - o * in;
-  float s = 0.f;
-  for (int c = 0; c < chunks; ++c)
-    s += part[((int64_t)c * out + o) * in_pad + i];
-  g[t] = s;
+static NetWeights weights(Mlp *m) {
+  NetWeights w;
+  for (int l = 0; l <= kLayers; ++l) w.W[l] = wb(m, l);
+  for (int l = 0; l < kLayers; ++l) w.Wt[l] = wtb(m, l);
+  return w;
 }
 
-__global__ void k_fill(float *p, float v, int64_t n) {
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (t < n) p[t] = v;
-}
-
-__global__ void k_copy_pad(const float *__restrict__ src, int n, int npad,
-                           float *__restrict__ dst) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  if (t < npad) dst[t] = t < n ? src[t] : 0.f;
-}
-
-__global__ void k_loss_final(const float *__restrict__ part, int nparts,
-                             float inv_n, float *__restrict__ out) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    float s = 0.f;
-    for (int i = 0; i < nparts; ++i) s += part[i];
-    out[0] = s * inv_n;
-  }
-}
-
-// Forward pass over rows [0, npad): activations and SiLU derivatives of
-// every hidden layer in the workspace; y [n] if given.
-static int forward(Mlp *m, int n, int npad, const float *x, float *y,
-                   hipStream_t s) {
-  const float *norm = reinterpret_cast<const float *>(m->norm.ptr);
+// Parameter gradient gp of the loss whose seed is 2 (y - tgt) / n or, when
+// dy is given, dy; and, if given, the mean squared residual and the
+// gradient of the inputs.
+static int gradients(Mlp *m, int n, const float *x, const float *tgt,
+                     const float *dy, float *gp, float *loss, float *grad_x,
+                     hipStream_t s) {
+  const int npad = (n + kRowTile - 1) / kRowTile * kRowTile;
+  int rc;
+  if ((rc = ws(m, npad, s))) return rc;
   uint16_t *a0 = reinterpret_cast<uint16_t *>(m->a0.ptr);
-  hipLaunchKernelGGL(k_mlp_input, dim3(blocks((int64_t)npad * kInPad, 256)),
-                     dim3(256), 0, s, x, n, npad, m->n_in, norm,
-                     norm + kInPad, a0);
-  const float *p = pf(m);
-  const unsigned g = (unsigned)(npad / 128);
-  const int ni = m->n_in;
-  hipLaunchKernelGGL(k_mlp_fwd<kInPad>, dim3(g), dim3(256), 0, s, a0,
-                     wb(m, 0), p + layer_desc(0, ni).b_off, actp(m, 1),
-                     dp(m, 0));
-  for (int l = 1; l < kLayers; ++l)
-    hipLaunchKernelGGL(k_mlp_fwd<kHid>, dim3(g), dim3(256), 0, s, actp(m, l),
-                       wb(m, l), p + layer_desc(l, ni).b_off, actp(m, l + 1),
-                       dp(m, l));
-  if (y)
-    hipLaunchKernelGGL(k_mlp_out, dim3(blocks(n, 256)), dim3(256), 0, s,
-                       actp(m, 4), wb(m, 4), p + layer_desc(4, ni).b_off,
-                       m->out_scale, n, y);
-  return check_launch(m->h, "mlp forward");
-}
-
-// Backward pass from seed [npad] (dLoss/dy, zero on padded rows).  With
-// gp, writes the parameter gradient; with grad_x, the input gradient.
-static int backward(Mlp *m, int n, int npad, float *gp, float *grad_x,
-                    hipStream_t s) {
-  const float *norm = reinterpret_cast<const float *>(m->norm.ptr);
-  const float *seed = reinterpret_cast<const float *>(m->seed.ptr);
+  uint16_t *act = reinterpret_cast<uint16_t *>(m->act.ptr);
+  uint16_t *dz = reinterpret_cast<uint16_t *>(m->dz.ptr);
+  float *seed = reinterpret_cast<float *>(m->seed.ptr);
   float *wpart = reinterpret_cast<float *>(m->wpart.ptr);
-  float *bpart = reinterpret_cast<float *>(m->bpart.ptr);
-  const int chunks = npad / kChunk;
-  const unsigned g = (unsigned)(npad / 128);
-  const int ni = m->n_in;
-  if (gp) {
-    hipLaunchKernelGGL(k_mlp_wgrad_out, dim3(chunks), dim3(256), 0, s, seed,
-                       m->out_scale, actp(m, 4), n, bpart);
-    hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(256), 0, s, bpart, chunks,
-                       kHid + 1, gp + layer_desc(4, ni).w_off);
-  }
-  hipLaunchKernelGGL(k_mlp_bwd_out, dim3(blocks((int64_t)npad * kHid, 256)),
-                     dim3(256), 0, s, seed, m->out_scale, wb(m, 4), dp(m, 3),
-                     npad, dzp(m, 3));
-  for (int l = kLayers - 1; l >= 0; --l) {
-    const LayerDesc d = layer_desc(l, ni);
-    if (gp) {
-      const uint16_t *A = l == 0 ? reinterpret_cast<const uint16_t *>(m->a0.ptr)
-                                 : actp(m, l);
-      if (l == 0)
-        hipLaunchKernelGGL(k_mlp_wgrad<kInPad>, dim3(chunks), dim3(256), 0, s,
-                           dzp(m, 0), A, wpart, bpart);
-      else
-        hipLaunchKernelGGL(k_mlp_wgrad<kHid>, dim3(chunks), dim3(256), 0, s,
-                           dzp(m, l), A, wpart, bpart);
-      hipLaunchKernelGGL(k_sum_w, dim3(blocks(kHid * d.in, 256)), dim3(256), 0,
-                         s, wpart, chunks, kHid, d.in, d.in_pad,
-                         gp + d.w_off);
-      hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(256), 0, s, bpart, chunks,
-                         kHid, gp + d.b_off);
-    }
-    if (l > 0)
-      hipLaunchKernelGGL(k_mlp_bwd<kHid>, dim3(g), dim3(256), 0, s, dzp(m, l),
-                         wtb(m, l), dp(m, l - 1), dzp(m, l - 1),
-                         norm + kInPad, n, ni, nullptr);
-    else if (grad_x)
-      hipLaunchKernelGGL(k_mlp_bwd<kInPad>, dim3(g), dim3(256), 0, s,
-                         dzp(m, 0), wtb(m, 0), nullptr, nullptr,
-                         norm + kInPad, n, ni, grad_x);
-  }
-  return check_launch(m->h, "mlp backward");
+  float *lpart = reinterpret_cast<float *>(m->lpart.ptr);
+  const int64_t stride = (int64_t)npad * kHid;
+  hipLaunchKernelGGL(k_mlp_train_rows, dim3(npad / kRowTile),
+                     dim3(64 * kRowWaves), 0, s, x, n, m->n_in,
+                     reinterpret_cast<const float *>(m->norm.ptr), weights(m),
+                     pf(m), m->out_scale, tgt, dy, a0, act, dz, stride, seed,
+                     lpart, grad_x);
+  const int chunks = chunk_count(npad);
+  hipLaunchKernelGGL(k_mlp_wgrad, dim3(chunks, 5), dim3(256), 0, s, a0, act,
+                     dz, stride, seed, npad, chunk_rows(npad), wpart);
+  hipLaunchKernelGGL(k_grad_sum, dim3(blocks(kPartLen, 64) + 1), dim3(256), 0,
+                     s, wpart, chunks, m->n_in, gp, lpart, npad / 32,
+                     1.f / (float)n, loss);
+  return check_launch(m->h, "mlp gradients");
 }
 
 static int check_rows(Mlp *m, int n, const void *x) {
@@ -189,24 +121,17 @@ static int check_rows(Mlp *m, int n, const void *x) {
   return PCSDF_OK;
 }
 
-static int pad_rows(int n) { return ((n + kChunk - 1) / kChunk) * kChunk; }
-
 // Fused inference (value and input gradient) of rows [0, n) (with n_dev,
-// [0, min(n, *n_dev)) read on the device): one workgroup per tile of
-// 32 * kInferRowBlocks rows, at most 2048 workgroups striding over tiles.
+// [0, min(n, *n_dev)) read on the device).
 static int mlp_infer(Mlp *m, int n, const int *n_dev, const float *x,
                      float *y, float *gx, hipStream_t s) {
-  NetWeights w;
-  for (int l = 0; l <= kLayers; ++l) w.W[l] = wb(m, l);
-  for (int l = 0; l < kLayers; ++l) w.Wt[l] = wtb(m, l);
-  constexpr int RB = kInferRowBlocks;
-  const int tiles = (n + 32 * RB - 1) / (32 * RB);
-  const int grid = tiles < 2048 ? tiles : 2048;
+  const int tiles = (n + kRowTile - 1) / kRowTile;
+  const int grid = std::min(tiles, kInferBlocks);
   if (grid == 0) return PCSDF_OK;
-  hipLaunchKernelGGL(k_mlp_infer<RB>, dim3(grid), dim3(256), 0, s, x, n,
-                     n_dev, m->n_in,
-                     reinterpret_cast<const float *>(m->norm.ptr), w, pf(m),
-                     m->out_scale, y, gx);
+  hipLaunchKernelGGL(k_mlp_infer, dim3(grid), dim3(64 * kRowWaves), 0, s, x,
+                     n, n_dev, m->n_in,
+                     reinterpret_cast<const float *>(m->norm.ptr), weights(m),
+                     pf(m), m->out_scale, y, gx);
   return check_launch(m->h, "mlp inference");
 }
 
@@ -267,10 +192,9 @@ extern "C" int pcsdf_mlp_create(pcsdf_handle *hp, int32_t n_in,
 
 extern "C" void pcsdf_mlp_destroy(pcsdf_mlp *m) {
   if (!m) return;
-  DevBuf *bufs[] = {&m->params, &m->grad, &m->m1,   &m->m2,    &m->wbf,
-                    &m->wtbf,   &m->norm, &m->wofs, &m->a0,    &m->act,
-                    &m->dact,   &m->dz,   &m->seed, &m->y,     &m->wpart,
-                    &m->bpart,  &m->lpart};
+  DevBuf *bufs[] = {&m->params, &m->grad, &m->m1,   &m->m2,  &m->wbf,
+                    &m->wtbf,   &m->norm, &m->wofs, &m->a0,  &m->act,
+                    &m->dz,     &m->seed, &m->wpart, &m->lpart};
   bool any = false;
   for (DevBuf *b : bufs) any = any || b->ptr;
   if (any) (void)hipDeviceSynchronize();
@@ -332,9 +256,6 @@ extern "C" int pcsdf_mlp_get_params(pcsdf_mlp *m, float *params_host) {
   return PCSDF_OK;
 }
 
-// Inference (value and input gradient) runs fused, one workgroup per tile
-// of 64 rows (mlp_fused.h); training keeps the layer-by-layer kernels,
-// whose stored activations the weight gradients need.
 extern "C" int pcsdf_mlp_forward(pcsdf_mlp *m, int32_t n, const float *x_dev,
                                  float *y_dev, float *grad_x_dev,
                                  void *stream) {
@@ -359,32 +280,8 @@ extern "C" int pcsdf_mlp_gradients(pcsdf_mlp *m, int32_t n,
   if (n == 0 || !dy_dev || !grad_params_dev)
     return fail(m->h, PCSDF_ERR_INVALID_ARG, "need n > 0, dy and grad");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  const int npad = pad_rows(n);
-  if ((rc = ws(m, npad, s))) return rc;
-  if ((rc = forward(m, n, npad, x_dev, nullptr, s))) return rc;
-  hipLaunchKernelGGL(k_copy_pad, dim3(blocks(npad, 256)), dim3(256), 0, s,
-                     dy_dev, n, npad, reinterpret_cast<float *>(m->seed.ptr));
-  return backward(m, n, npad, grad_params_dev, grad_x_dev, s);
-}
-
-// dLoss/dparams of the mean squared error into gp [nparam] (and the loss
-// into loss_dev): the forward pass, k_mse's seed and the backward pass.
-static int loss_gradients(Mlp *m, int n, const float *x_dev,
-                          const float *target_dev, float *gp,
-                          float *loss_dev, hipStream_t s) {
-  const int npad = pad_rows(n);
-  int rc;
-  if ((rc = ws(m, npad, s))) return rc;
-  float *y = reinterpret_cast<float *>(m->y.ptr);
-  if ((rc = forward(m, n, npad, x_dev, y, s))) return rc;
-  float *lpart = reinterpret_cast<float *>(m->lpart.ptr);
-  hipLaunchKernelGGL(k_mse, dim3(blocks(npad, 256)), dim3(256), 0, s, y,
-                     target_dev, n, npad,
-                     reinterpret_cast<float *>(m->seed.ptr), lpart);
-  if (loss_dev)
-    hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(64), 0, s, lpart,
-                       (int)blocks(npad, 256), 1.f / (float)n, loss_dev);
-  return backward(m, n, npad, gp, nullptr, s);
+  return gradients(m, n, x_dev, nullptr, dy_dev, grad_params_dev, nullptr,
+                   grad_x_dev, s);
 }
 
 // One bias-corrected Adam step from the gradient g (device, fp32
@@ -427,8 +324,8 @@ extern "C" int pcsdf_mlp_loss_gradients(pcsdf_mlp *m, int32_t n,
   if (((uintptr_t)x_dev | (uintptr_t)target_dev | (uintptr_t)grad_params_dev |
        (uintptr_t)loss_dev) & 3)
     return fail(m->h, PCSDF_ERR_ALIGN, "device buffers must be 4-byte aligned");
-  return loss_gradients(m, n, x_dev, target_dev, grad_params_dev, loss_dev,
-                        s);
+  return gradients(m, n, x_dev, target_dev, nullptr, grad_params_dev,
+                   loss_dev, nullptr, s);
 }
 
 extern "C" int pcsdf_mlp_adam_step(pcsdf_mlp *m, const float *grad_params_dev,
@@ -459,7 +356,8 @@ extern "C" int pcsdf_mlp_train_step(pcsdf_mlp *m, int32_t n,
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   ProfScope ps(m->h, PCSDF_KERNEL_MLP_TRAIN, s);
   float *gp = reinterpret_cast<float *>(m->grad.ptr);
-  if ((rc = loss_gradients(m, n, x_dev, target_dev, gp, loss_dev, s)))
+  if ((rc = gradients(m, n, x_dev, target_dev, nullptr, gp, loss_dev, nullptr,
+                      s)))
     return rc;
   return adam(m, gp, lr, beta1, beta2, eps, s);
 }
