@@ -387,7 +387,7 @@ def measure_workload(pc, autotune, torch, dev, sc, name: str, steps: int,
     alg_bytes = (8.0 + 4.0 / n) * V * n
     achieved = alg_bytes / comp_avg_s / 1e9
     # the library's rule for the copy (pcsdf_tuning.composite_static16)
-    G = min(tuning.get("composite_slices_per_block") or 2, n)
+    G = min(tuning.get("composite_slices_per_block") or 1, n)
     order = int(tuning.get("composite_order") or 0)
     c16 = tuning.get("composite_static16", 0)
     copy16 = c16 == 2 or (c16 == 0 and V >= 1 << 25 and -(-n // G) >= 4)

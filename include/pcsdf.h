@@ -156,8 +156,7 @@ int pcsdf_build_floor_sdf(pcsdf_handle *h, const pcsdf_grid *grid,
  * Errors: PCSDF_ERR_NUMERIC for non-finite inputs or when a fixed-point
  * value reaches 2^62 in magnitude or R reaches 2^31.
  * Uses a workspace of 8*n_slices*nx*ny + 24*n_slices*n_humans*ny bytes,
- * plus 2*V bytes for the 16-bit static copy (see pcsdf_tuning) when the
- * outputs are written in per-slice packs of 4, 2 or 1 voxels. */
+ * plus 2*V bytes for the 16-bit static copy (see pcsdf_tuning). */
 int pcsdf_predicted_composite_sdf(pcsdf_handle *h, const pcsdf_grid *grid,
                                   const int32_t *static_ssq_dev,
                                   int32_t n_slices, int32_t n_humans,
@@ -318,7 +317,10 @@ typedef struct pcsdf_scene {
 /* Launch shapes (0 = library default).  Chosen by the autotuner
  * (pcsdf_autotune_*) or set directly. */
 typedef struct pcsdf_tuning {
-  int32_t composite_slices_per_block; /* composite: slices per block row */
+  int32_t composite_slices_per_block; /* composite: slices per block row;
+                                         0: one, or two where only one
+                                         field is written, in the order
+                                         1 below */
   int32_t batch_slices_per_item;      /* batch: slices per composite item */
   int32_t batch_chunk_quads;          /* batch: voxel quads per composite
                                          item, a multiple of 256 */
@@ -330,11 +332,14 @@ typedef struct pcsdf_tuning {
                                          (one wave each) per column, 1, 2,
                                          4 or 8; 0: one per 32 voxels of
                                          the column, at most 8 */
-  int32_t composite_order;            /* composite: 0 (default) blocks in
-                                         flight write the same few slices
-                                         over consecutive voxel chunks; 1
-                                         the slice groups of a chunk run in
-                                         succession on one XCD and re-read
+  int32_t composite_order;            /* composite, with slices per block
+                                         row chosen: 0 blocks in flight
+                                         write the same few slices over
+                                         consecutive voxel chunks; 1 the
+                                         slice groups of a chunk run in
+                                         succession on one XCD, within
+                                         spans of as many slices as the
+                                         grid's size allows, and re-read
                                          its static values from L2 */
   int32_t composite_static16;         /* composite: 1 the slice groups read
                                          the static field; 2 a 16-bit copy
@@ -342,8 +347,8 @@ typedef struct pcsdf_tuning {
                                          values beyond +-32767 are read
                                          from the field), in the handle's
                                          workspace (2 B per voxel); 0 the
-                                         copy for grids of at least 2^25
-                                         voxels with at least 4 slice
+                                         copy for grids of at least 2^26
+                                         voxels with at least 24 slice
                                          groups */
 } pcsdf_tuning;
 

@@ -99,11 +99,11 @@ def build_floor_sdf(grid, occ, z_lo=0, z_hi=None, want_sdf=True,
 def composite_outputs(n, shape_zyx, device, want_ssq=True, want_sdf=True):
     """Output fields [n, nz, ny, nx] (int32 squared voxel distance, fp32
     metres) as the composite calls allocate them by default: both in one
-    allocation, the fp32 field starting 4 KiB past the end of the int32
-    one.  Two output streams whose starts differ by a multiple of 8 KiB (as
+    allocation, the fp32 field starting on the first 128-byte line at least
+    4 KiB past the end of the int32 one (so that both start on a line: the
+    kernel cuts its packs at the lines of one of them).  Two output streams whose starts differ by a multiple of 8 KiB (as
     two separate large allocations do) write measurably more slowly on
-    this GPU (256x256x128 x 20 slices: 0.239 against 0.231 ms).  The fp32
-    field keeps the 16-byte alignment the widest packs need."""
+    this GPU (256x256x128 x 20 slices: 0.239 against 0.231 ms)."""
     torch = _torch()
     cnt = int(n)
     for d in shape_zyx:
@@ -115,7 +115,7 @@ def composite_outputs(n, shape_zyx, device, want_ssq=True, want_sdf=True):
         of = torch.empty(shp, dtype=torch.float32, device=device) \
             if want_sdf else None
         return oc, of
-    pad = 1024  # int32 elements: 4 KiB
+    pad = 1024 + -cnt % 32  # int32 elements: 4 KiB, up to a line
     buf = torch.empty(2 * cnt + pad, dtype=torch.int32, device=device)
     oc = buf[:cnt].view(shp)
     of = buf[cnt + pad:].view(torch.float32).view(shp)

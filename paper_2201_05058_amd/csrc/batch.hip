@@ -63,8 +63,10 @@ static int enqueue_batch(Handle *h, const BatchPlan &bp, char *pbase,
     if (rc) return rc;
   }
   if (nc > 0) {
-    const int64_t grid = bp.blocks_cu > 0 ? std::min<int64_t>(nc, bp.blocks_cu)
-                                          : nc;
+    // at most 2^23 workgroups (a launch holds 2^32 threads), which then
+    // stride over the items
+    const int64_t grid =
+        std::min<int64_t>(nc, bp.blocks_cu > 0 ? bp.blocks_cu : 1 << 23);
     hipLaunchKernelGGL(k_batch_composites, dim3((unsigned)grid), dim3(256), 0,
                        s, scenes, scene_of, bp.composite_items, bp.G,
                        bp.chunk_voxels);

@@ -23,11 +23,14 @@ struct SceneDev {
   int64_t R;
   uint32_t V;
   int nx, ny, nz, n, K, Kt, has_above;
-  int vec, gather;  // pack shape of the composite (composite_shape)
+  int aligned;  // every composite pack is aligned (packs_aligned)
   float hf;
   uint32_t item0;   // first composite item of the scene
   uint32_t items;   // its composite items: slice groups x chunks
-  uint32_t chunks;  // voxel chunks per slice group
+  uint32_t chunks;  // voxel chunks per slice group, a multiple of eight
+  uint32_t span;    // slice groups per span of items
+  FastDiv plane;    // nx ny
+  FastDiv per_span, per_oct;  // items per span, per octet of chunks in one
 };
 
 // Composite items are numbered scene by scene, each scene's count padded
@@ -42,6 +45,13 @@ constexpr int kItemGroup = 1 << kItemGroupShift;
 // (a wait for a flat access cannot be counted in order and so waits for
 // all outstanding loads and stores).  A whole-struct copy would lose the
 // address space.
+template <class T>
+__device__ __forceinline__ void load_div(FastDiv *d, T *c) {
+  d->d = c->d;
+  d->m = c->m;
+  d->s1 = c->s1;
+  d->s2 = c->s2;
+}
 __device__ __forceinline__ SceneDev load_scene(const SceneDev *scenes, int q) {
 #if defined(__clang__)
   typedef __attribute__((address_space(4))) const SceneDev ConstScene;
@@ -66,12 +76,15 @@ __device__ __forceinline__ SceneDev load_scene(const SceneDev *scenes, int q) {
   d.K = c->K;
   d.Kt = c->Kt;
   d.has_above = c->has_above;
-  d.vec = c->vec;
-  d.gather = c->gather;
+  d.aligned = c->aligned;
   d.hf = c->hf;
   d.item0 = c->item0;
   d.items = c->items;
   d.chunks = c->chunks;
+  d.span = c->span;
+  load_div(&d.plane, &c->plane);
+  load_div(&d.per_span, &c->per_span);
+  load_div(&d.per_oct, &c->per_oct);
   return d;
 }
 
@@ -144,33 +157,37 @@ __device__ inline void plane_item(const SceneDev &sc, int s, int tile,
   }
 }
 
-// Composite of `count` consecutive voxels from v0 (VEC voxels per lane)
-// for slices [s0, s1); v0 is a multiple of the chunk size, itself a
-// multiple of 4.  Each lane runs the same epilogue as the single-scene
-// kernel; with the tuned chunk of 256 lanes x 4 voxels a lane handles one
-// pack and exits.  (A loop that loads the next step's data ahead of the
-// current stores was measured slower for these short item lengths, and
-// persistent grids slower than one workgroup per item.)
-template <int VEC, bool kGather, bool kSsq, bool kSdf>
+// Composite of `count` consecutive voxels from v0 (four per lane) for slices
+// [s0, s1); v0 is a multiple of the chunk size, itself a multiple of 4.
+// Each lane runs the same epilogue as the single-scene kernel; with the
+// tuned chunk of 256 lanes x 4 voxels a lane handles one pack and exits.
+// (A loop that loads the next step's data ahead of the current stores was
+// measured slower for these short item lengths, and persistent grids
+// slower than one workgroup per item.)
+template <bool kAligned, bool kSsq, bool kSdf>
 __device__ inline void composite_chunk(const SceneDev &sc, uint32_t v0,
                                        uint32_t count, int s0, int s1) {
-  const uint32_t plane = (uint32_t)sc.nx * (uint32_t)sc.ny;
-  const uint32_t end = min(sc.V, v0 + count);
-  for (uint32_t v = v0 + threadIdx.x * VEC; v < end; v += blockDim.x * VEC)
-    composite_pack<VEC, kGather, kSsq, kSdf>(sc.S, sc.P, nullptr, sc.oc,
-                                             sc.of, plane, sc.V, v, s0, s1,
-                                             sc.Kt, sc.has_above, sc.hf);
+  const uint32_t end = min(pack_span(sc.V, kAligned), v0 + count);
+  for (uint32_t v = v0 + threadIdx.x * 4; v < end; v += blockDim.x * 4) {
+    if (kAligned)
+      composite_pack<kSsq, kSdf>(sc.S, sc.P, nullptr, sc.oc, sc.of, sc.plane,
+                                 sc.V, v, s0, s1, sc.Kt, sc.has_above, sc.hf);
+    else
+      composite_pack_shifted<kSsq, kSdf>(sc.S, sc.P, nullptr, sc.oc, sc.of,
+                                         sc.plane, sc.V, v, s0, s1, sc.Kt,
+                                         sc.has_above, sc.hf);
+  }
 }
 
-template <int VEC, bool kGather>
+template <bool kAligned>
 __device__ inline void composite_chunk_any(const SceneDev &sc, uint32_t v0,
                                            uint32_t count, int s0, int s1) {
   if (sc.oc && sc.of)
-    composite_chunk<VEC, kGather, true, true>(sc, v0, count, s0, s1);
+    composite_chunk<kAligned, true, true>(sc, v0, count, s0, s1);
   else if (sc.oc)
-    composite_chunk<VEC, kGather, true, false>(sc, v0, count, s0, s1);
+    composite_chunk<kAligned, true, false>(sc, v0, count, s0, s1);
   else
-    composite_chunk<VEC, kGather, false, true>(sc, v0, count, s0, s1);
+    composite_chunk<kAligned, false, true>(sc, v0, count, s0, s1);
 }
 
 // Workers.  A grid strides over a list of work items; nothing waits on
@@ -188,9 +205,11 @@ __device__ inline void batch_planes(const SceneDev *__restrict__ scenes,
   }
 }
 
-// Composite item `it` belongs to scene q = scene_of[it / kItemGroup]; it
-// is slice group (it - item0) / chunks and voxel chunk (it - item0) %
-// chunks of that scene, or padding when it - item0 >= items.
+// Composite item `it` belongs to scene q = scene_of[it / kItemGroup]; its
+// number within the scene, it - item0 (item0 is a multiple of eight), counts
+// spans, octets of chunks, the span's slice groups and the octet's chunks,
+// the last fastest (the order of slices_per_span's comment); it is padding
+// when it - item0 >= items.
 __device__ inline void batch_composites(const SceneDev *__restrict__ scenes,
                                         const int32_t *__restrict__ scene_of,
                                         uint32_t total, int G,
@@ -199,20 +218,18 @@ __device__ inline void batch_composites(const SceneDev *__restrict__ scenes,
     const SceneDev sc = load_scene(scenes, scene_of[it >> kItemGroupShift]);
     const uint32_t local = it - sc.item0;
     if (local >= sc.items) continue;
-    const uint32_t sg = local / sc.chunks;
-    const uint32_t v0 = (local - sg * sc.chunks) * chunk_voxels;
-    const int s0 = (int)sg * G;
+    const uint32_t sp = quotient(local, sc.per_span);
+    const uint32_t in_span = local - sp * sc.per_span.d;
+    const uint32_t oct = quotient(in_span, sc.per_oct);
+    const uint32_t in_oct = in_span - oct * sc.per_oct.d;
+    const uint32_t v0 = (oct * 8 + (in_oct & 7)) * chunk_voxels;
+    const int s0 = (int)((sp * sc.span + (in_oct >> 3)) * (uint32_t)G);
     const int s1 = min(sc.n, s0 + G);
-    if (sc.vec == 4 && !sc.gather)
-      composite_chunk_any<4, false>(sc, v0, chunk_voxels, s0, s1);
-    else if (sc.vec == 4)
-      composite_chunk_any<4, true>(sc, v0, chunk_voxels, s0, s1);
-    else if (sc.vec == 2 && !sc.gather)
-      composite_chunk_any<2, false>(sc, v0, chunk_voxels, s0, s1);
-    else if (sc.vec == 2)
-      composite_chunk_any<2, true>(sc, v0, chunk_voxels, s0, s1);
+    if (s0 >= s1 || v0 >= pack_span(sc.V, sc.aligned)) continue;
+    if (sc.aligned)
+      composite_chunk_any<true>(sc, v0, chunk_voxels, s0, s1);
     else
-      composite_chunk_any<1, false>(sc, v0, chunk_voxels, s0, s1);
+      composite_chunk_any<false>(sc, v0, chunk_voxels, s0, s1);
   }
 }
 

@@ -21,7 +21,7 @@ struct BatchPlan {
   std::vector<int64_t> xy;
   std::vector<size_t> xy_off;  // per scene, in int64 units
   int lds_cap = 0;
-  int G = 2;
+  int G = 1;
   uint32_t chunk_voxels = 0;
   int blocks = 0;     // persistent grid of the planar launch
   int blocks_cu = 0;  // persistent composite grid (0: one item per block)
@@ -36,12 +36,38 @@ inline bool fixed(double p, double o, double h, int64_t *out) {
   return true;
 }
 
+// Numbers the composite items of every scene for the plan's slices per item
+// and chunk; returns their count including padding (more than 2^31 - 1: the
+// scenes' numbers are not usable).
+inline int64_t count_items(BatchPlan *bp) {
+  int64_t next = 0;
+  for (SceneDev &d : bp->scenes) {
+    const int64_t chunks =
+        ((int64_t)pack_span(d.V, d.aligned) + bp->chunk_voxels - 1) /
+        bp->chunk_voxels;
+    d.chunks = (uint32_t)((chunks + 7) / 8 * 8);
+    // spans of the single composite's length, whole slice groups each
+    const int groups = (d.n + bp->G - 1) / bp->G;
+    d.span = (uint32_t)std::max(
+        1, (slices_per_span(d.V, d.n, false) + bp->G - 1) / bp->G);
+    const int64_t ct = (int64_t)((groups + (int)d.span - 1) / (int)d.span) *
+                       d.span * d.chunks;
+    d.plane = fast_div((uint32_t)d.nx * (uint32_t)d.ny);
+    d.per_span = fast_div(d.span * d.chunks);
+    d.per_oct = fast_div(d.span * 8);
+    d.item0 = (uint32_t)next;
+    d.items = (uint32_t)ct;
+    next += (ct + kItemGroup - 1) / kItemGroup * kItemGroup;
+  }
+  return next;
+}
+
 // Validates the scenes and fills everything but device addresses.
 inline int plan_batch(Handle *h, int n_scenes, const pcsdf_scene *scenes,
                       const pcsdf_tuning &tu, int n_cu, BatchPlan *bp) {
   if (n_scenes < 1 || !scenes)
     return fail(h, PCSDF_ERR_INVALID_ARG, "need at least one scene");
-  bp->G = tu.batch_slices_per_item > 0 ? tu.batch_slices_per_item : 4;
+  bp->G = tu.batch_slices_per_item > 0 ? tu.batch_slices_per_item : 1;
   const int quads = tu.batch_chunk_quads > 0 ? tu.batch_chunk_quads : 256;
   bp->chunk_voxels = (uint32_t)quads * 4;
   bp->blocks = n_cu * (tu.batch_blocks_per_cu > 0 ? tu.batch_blocks_per_cu
@@ -86,11 +112,9 @@ inline int plan_batch(Handle *h, int n_scenes, const pcsdf_scene *scenes,
     d.has_above = d.Kt + 1 <= d.nz - 1;
     d.K = (d.Kt < 0) ? 0 : in.n_humans;
     d.hf = (float)hv;
-    const PackShape ps =
-        composite_shape((int64_t)d.nx * d.ny, (int64_t)d.V, in.static_ssq_dev,
-                        in.out_ssq_dev, in.out_sdf_dev);
-    d.vec = ps.vec;
-    d.gather = ps.gather;
+    d.aligned = packs_aligned((int64_t)d.nx * d.ny, (int64_t)d.V,
+                              in.static_ssq_dev, in.out_ssq_dev,
+                              in.out_sdf_dev);
     bp->xy_off[q] = bp->xy.size();
     for (int64_t t = 0; t < (int64_t)in.n_slices * in.n_humans; ++t) {
       int64_t X, Y;
@@ -107,13 +131,24 @@ inline int plan_batch(Handle *h, int n_scenes, const pcsdf_scene *scenes,
     lds_need = std::max(lds_need, d.K * 16 + d.K * d.ny * 8);
   }
   bp->lds_cap = std::min(lds_need, 48 * 1024);
-  // planar items (tiles of a slice when its chords fit in LDS),
-  // scene-major; composite items are counted per scene
+  // composite items, counted per scene; a batch with too many of the default
+  // size gets longer ones
+  int64_t next = count_items(bp);
+  while (next > (int64_t)INT32_MAX && tu.batch_slices_per_item == 0 &&
+         bp->G < (1 << 20)) {
+    bp->G *= 4;
+    next = count_items(bp);
+  }
+  if (next > (int64_t)INT32_MAX)
+    return fail(h, PCSDF_ERR_DIMS,
+                "batch has more than 2^31 - 1 composite items; raise the "
+                "chunk size or split the batch");
+  // planar items (tiles of a slice when its chords fit in LDS) and the
+  // scene of each group of composite items, scene-major
   bp->items.clear();
   bp->scene_of.clear();
-  int64_t next = 0;
   for (int q = 0; q < n_scenes; ++q) {
-    SceneDev &d = bp->scenes[q];
+    const SceneDev &d = bp->scenes[q];
     const int64_t npx = (int64_t)d.nx * d.ny;
     const int tiles = chords_in_lds(d.K, d.ny, bp->lds_cap)
                           ? (int)((npx + kPlaneTile - 1) / kPlaneTile)
@@ -121,19 +156,8 @@ inline int plan_batch(Handle *h, int n_scenes, const pcsdf_scene *scenes,
     for (int s = 0; s < d.n; ++s)
       for (int t = 0; t < tiles; ++t)
         bp->items.push_back(make_int4(kItemPlane, q, s, t));
-    const int64_t chunks =
-        ((int64_t)d.V + bp->chunk_voxels - 1) / bp->chunk_voxels;
-    const int64_t ct = (int64_t)((d.n + bp->G - 1) / bp->G) * chunks;
-    const int64_t padded = (ct + kItemGroup - 1) / kItemGroup * kItemGroup;
-    if (next + padded > (int64_t)INT32_MAX)
-      return fail(h, PCSDF_ERR_DIMS,
-                  "batch has more than 2^31 - 1 composite items; raise the "
-                  "chunk size or split the batch");
-    d.item0 = (uint32_t)next;
-    d.items = (uint32_t)ct;
-    d.chunks = (uint32_t)chunks;
-    bp->scene_of.insert(bp->scene_of.end(), (size_t)(padded / kItemGroup), q);
-    next += padded;
+    bp->scene_of.insert(bp->scene_of.end(),
+                        ((size_t)d.items + kItemGroup - 1) / kItemGroup, q);
   }
   bp->composite_items = (uint32_t)next;
   if (bp->items.size() > (size_t)INT32_MAX)

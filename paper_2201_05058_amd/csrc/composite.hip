@@ -27,10 +27,8 @@
 //   and write both outputs.
 // The epilogue moves the compulsory bytes only: 4 B of static field per
 // voxel (read once for all slices) and 8 B per voxel-slice of output; the
-// planes (nx*ny*4 B per slice) stay in cache.  When V is odd a pack of one
-// slice's voxels would start at a different alignment in every slice, so
-// k_composite_flat walks the flattened outputs [n][V] in aligned packs
-// instead, reading the static field per voxel-slice.
+// planes (nx*ny*4 B per slice) stay in cache.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -64,152 +62,76 @@ __global__ __launch_bounds__(256) void k_static16(
 }
 
 // Slices with need[sl] == 0 are skipped when `need` is non-null.  Thread g
-// handles voxels VEC g .. VEC g + VEC - 1 (VEC divides V); kGather reads
-// their planar values one by one (VEC does not divide nx ny); with S16
-// the static values come from the 16-bit copy.
-template <int VEC, bool kGather, bool kSsq, bool kSdf>
+// handles the packs at voxel 4 g (composite_pack, or with !kAligned
+// composite_pack_shifted); with S16 the static values come from the 16-bit
+// copy.
+template <bool kAligned, bool kSsq, bool kSdf>
 __global__ __launch_bounds__(256) void k_composite(
     const int32_t *__restrict__ S, const int32_t *__restrict__ P,
     const int32_t *__restrict__ need,
-    int32_t *__restrict__ oc, float *__restrict__ of, uint32_t plane,
+    int32_t *__restrict__ oc, float *__restrict__ of, FastDiv plane,
     int n_slices, int G, int Kt, int has_above, float hf, uint32_t V,
-    int order, const int16_t *__restrict__ S16) {
-  // order 0: block (chunk, group) = (blockIdx.x, blockIdx.y), so the
-  // blocks in flight write the same few slices over consecutive chunks.
-  // order 1 (one-dimensional grid): blocks 8 apart take chunks x, x + 8,
-  // ... (x = block mod 8) and, for each, its slice groups one after the
-  // other.  The dispatcher places block b on XCD b mod 8, so the groups of
-  // a chunk run on one XCD in close succession and re-read the chunk's
-  // static field from that XCD's L2 rather than from HBM; in exchange the
-  // blocks in flight write every slice at once.
-  uint32_t chunk, grp;
-  if (order) {
-    const uint32_t ng = (uint32_t)((n_slices + G - 1) / G);
-    const uint32_t j = blockIdx.x >> 3, cj = j / ng;
-    grp = j - cj * ng;
-    chunk = cj * 8 + (blockIdx.x & 7);
-  } else {
-    chunk = blockIdx.x;
-    grp = blockIdx.y;
-  }
-  const uint32_t g = chunk * 256u + threadIdx.x;
-  const uint32_t v0 = g * VEC;
-  if (v0 >= V) return;
-  const int s_begin = (int)grp * G;
+    FastDiv parts, const int16_t *__restrict__ S16) {
+  // The order of slices_per_span's comment: blockIdx.x is the XCD plus eight
+  // times the slice group within its span, y the chunk's octet, z the span
+  // (times the parts of the octets where y holds too few, `parts`).
+  const uint32_t sp = quotient(blockIdx.z, parts);
+  const uint32_t oct =
+      blockIdx.y + gridDim.y * (blockIdx.z - sp * parts.d);
+  const uint32_t chunk = oct * 8 + (blockIdx.x & 7);
+  const uint32_t v0 = (chunk * 256u + threadIdx.x) * 4;
+  if (v0 >= pack_span(V, kAligned)) return;
+  const int s_begin = (int)(sp * (gridDim.x >> 3) + (blockIdx.x >> 3)) * G;
   const int s_end = min(n_slices, s_begin + G);
+  if (s_begin >= s_end) return;
   if (need) {  // skip the static read when none of the block's slices is due
     bool any = false;
     for (int sl = s_begin; sl < s_end; ++sl) any = any || need[sl] != 0;
     if (!any) return;
   }
-  if (need)
-    composite_pack<VEC, kGather, kSsq, kSdf, true>(
-        S, P, need, oc, of, plane, V, v0, s_begin, s_end, Kt, has_above, hf);
-  else
-    composite_pack<VEC, kGather, kSsq, kSdf, false>(
-        S, P, need, oc, of, plane, V, v0, s_begin, s_end, Kt, has_above, hf,
-        S16);
+#define PCSDF_PACK(fn, kNeed, copy)                                       \
+  fn<kSsq, kSdf, kNeed>(S, P, need, oc, of, plane, V, v0, s_begin, s_end, \
+                        Kt, has_above, hf, copy)
+  if constexpr (kAligned) {
+    if (need)
+      PCSDF_PACK(composite_pack, true, nullptr);
+    else
+      PCSDF_PACK(composite_pack, false, S16);
+  } else {
+    if (need)
+      PCSDF_PACK(composite_pack_shifted, true, nullptr);
+    else
+      PCSDF_PACK(composite_pack_shifted, false, S16);
+  }
+#undef PCSDF_PACK
 }
 
-template <int VEC, bool kGather>
+template <bool kAligned>
 static void launch_comp(Handle *h, const int32_t *S, const int32_t *P,
                         const int32_t *need, int32_t *oc, float *of,
-                        uint32_t plane, int n, int G, int Kt, int has_above,
-                        float hf, uint32_t V, const int16_t *S16,
-                        hipStream_t s) {
-  const uint32_t nthreads = V / VEC;
-  const uint64_t chunks = (nthreads + 255) / 256, ng = (n + G - 1) / G;
-  const uint64_t flat = (chunks + 7) / 8 * 8 * ng;
-  const int order = h->tuning.composite_order == 1 && flat < (1ull << 31);
-  const dim3 grid = order ? dim3((unsigned)flat) : dim3((unsigned)chunks,
-                                                        (unsigned)ng);
+                        uint32_t plane, int n, int G, int span, int Kt,
+                        int has_above, float hf, uint32_t V,
+                        const int16_t *S16, hipStream_t s) {
+  const uint32_t nthreads = (pack_span(V, kAligned) + 3) / 4;
+  const uint32_t octets = ((nthreads + 255) / 256 + 7) / 8;
+  const int groups = (n + G - 1) / G;
+  const uint32_t parts = (octets + 65534) / 65535;
+  const dim3 grid(8 * (uint32_t)span, (octets + parts - 1) / parts,
+                  (unsigned)((groups + span - 1) / span) * parts);
   const dim3 block(256);
+  const FastDiv pd = fast_div(plane);
   if (oc && of)
-    launch_timed(h, k_composite<VEC, kGather, true, true>, grid, block, 0u,
-                 s, S, P, need, oc, of, plane, n, G, Kt, has_above, hf, V,
-                 order, S16);
+    launch_timed(h, k_composite<kAligned, true, true>, grid, block, 0u, s, S,
+                 P, need, oc, of, pd, n, G, Kt, has_above, hf, V, fast_div(parts),
+                 S16);
   else if (oc)
-    launch_timed(h, k_composite<VEC, kGather, true, false>, grid, block, 0u,
-                 s, S, P, need, oc, of, plane, n, G, Kt, has_above, hf, V,
-                 order, S16);
+    launch_timed(h, k_composite<kAligned, true, false>, grid, block, 0u, s, S,
+                 P, need, oc, of, pd, n, G, Kt, has_above, hf, V, fast_div(parts),
+                 S16);
   else
-    launch_timed(h, k_composite<VEC, kGather, false, true>, grid, block, 0u,
-                 s, S, P, need, oc, of, plane, n, G, Kt, has_above, hf, V,
-                 order, S16);
-}
-
-// The same composite over the flattened outputs [n][V] in aligned packs of
-// four, for grids whose V is odd (so that a pack of one slice's voxels
-// would start at a different alignment in every slice).
-// Pack t holds flat positions 4t .. 4t+3, each its own (slice, voxel): the
-// static field is read per voxel-slice (from the caches for the slices
-// after the first) so that every store is one aligned 16-byte pack.  The
-// output bases are 16-byte aligned; a last partial pack is stored element
-// by element.  N = n V < 2^32 - 4.
-template <bool kSsq, bool kSdf>
-__global__ __launch_bounds__(256) void k_composite_flat(
-    const int32_t *__restrict__ S, const int32_t *__restrict__ P,
-    int32_t *__restrict__ oc, float *__restrict__ of, uint32_t plane,
-    uint32_t V, uint64_t N, int Kt, int has_above, float hf) {
-  typedef uint32_t U;
-  const U t = (U)blockIdx.x * 256u + threadIdx.x;
-  const U f0 = t * 4u;
-  if ((uint64_t)f0 >= N) return;
-  U sl = f0 / V;
-  uint32_t v = (uint32_t)(f0 - sl * V);
-  uint32_t k = v / plane;
-  uint32_t pix = v - k * plane;
-  pk_i32x4 c;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    if ((uint64_t)f0 + e < N) {
-      const int32_t p = P[(size_t)sl * plane + pix];
-      c[e] = min(S[v], human_value(p, human_layer((int)k, Kt, has_above)));
-    } else {
-      c[e] = 0;
-    }
-    // next flat position (V may be below four: a pack may span slices)
-    ++v;
-    if (++pix == plane) {
-      pix = 0;
-      ++k;
-    }
-    while (v >= V) {
-      v -= V;
-      ++sl;
-      k = v / plane;
-      pix = v - k * plane;
-    }
-  }
-  pk_f32x4 fv;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) fv[e] = ssq_to_metres(c[e], hf);
-  if ((uint64_t)f0 + 4 <= N) {
-    if (kSsq) store_i32<4>(oc + f0, c);
-    if (kSdf) store_f32<4>(of + f0, fv);
-  } else {
-    for (int e = 0; (uint64_t)f0 + e < N; ++e) {
-      if (kSsq) oc[f0 + e] = c[e];
-      if (kSdf) of[f0 + e] = fv[e];
-    }
-  }
-}
-
-static void launch_comp_flat(Handle *h, const int32_t *S, const int32_t *P,
-                             int32_t *oc, float *of, uint32_t plane,
-                             uint32_t V, uint64_t N, int Kt, int has_above,
-                             float hf, hipStream_t s) {
-  const uint64_t packs = (N + 3) / 4;
-  const dim3 grid((unsigned)((packs + 255) / 256)), block(256);
-  if (oc && of)
-    launch_timed(h, k_composite_flat<true, true>, grid, block, 0u, s,
-                 S, P, oc, of, plane, V, N, Kt, has_above, hf);
-  else if (oc)
-    launch_timed(h, k_composite_flat<true, false>, grid, block, 0u,
-                 s, S, P, oc, of, plane, V, N, Kt, has_above, hf);
-  else
-    launch_timed(h, k_composite_flat<false, true>, grid, block, 0u,
-                 s, S, P, oc, of, plane, V, N, Kt, has_above, hf);
+    launch_timed(h, k_composite<kAligned, false, true>, grid, block, 0u, s, S,
+                 P, need, oc, of, pd, n, G, Kt, has_above, hf, V, fast_div(parts),
+                 S16);
 }
 
 // Fixed-point conversion of a coordinate to the 2^-16 voxel lattice:
@@ -381,14 +303,16 @@ int composite_run(Handle *h, const pcsdf_grid *g,
                           s, true);
 }
 
-// Whether the per-slice packs read the 16-bit static copy: the tuning's
-// choice, else when they read a static field of at least kStatic16Voxels
-// voxels for at least kStatic16Groups slice groups (the copy costs 6 B per
-// voxel once and saves 2 B per voxel and group; a smaller field is
-// re-read from the caches, where the copy was measured to gain nothing:
-// 256x256x128 x 20 slices).
-constexpr int kStatic16Groups = 4;
-constexpr int64_t kStatic16Voxels = 1LL << 25;
+// Whether the packs read the 16-bit static copy: the tuning's choice, else
+// when they read a static field of at least kStatic16Voxels voxels for at
+// least kStatic16Groups slice groups.  The copy costs 6 B per voxel once
+// (66 us at 67 M voxels) and saves 2 B per voxel and group, about 3.4 us a
+// group there: 67 M voxels x 50 slices 4.36 ms with it and 4.46 without, x
+// 10 slices 0.93 and 0.88.  At 33 M voxels the spans' re-reads already come
+// from the caches (x 40 slices 1.66 against 1.67 ms before the copy's own
+// 43 us).
+constexpr int kStatic16Groups = 24;
+constexpr int64_t kStatic16Voxels = 1LL << 26;
 static bool use_static16(const Handle *h, int64_t V, int groups) {
   const int t = h->tuning.composite_static16;
   return t == 2 ||
@@ -404,31 +328,29 @@ int launch_composite(Handle *h, const pcsdf_grid *g,
   const int64_t V = (int64_t)nx * ny * nz;
   // Streaming epilogue over all voxels and slices.
   const float hf = (float)g->voxel_m;
-  const PackShape ps = composite_shape((int64_t)nx * ny, V, static_ssq_dev,
-                                       out_ssq_dev, out_sdf_dev);
-  // Slices per block row: consecutive blocks write the same slices, which
-  // keeps the concurrent write streams few and contiguous.
-  int G = h->tuning.composite_slices_per_block > 0
-              ? h->tuning.composite_slices_per_block
-              : 2;
-  if (G > n_slices) G = n_slices;
-  while ((n_slices + G - 1) / G > 65535) ++G;
+  // Slices per block and slice groups per span: the rule's span of blocks of
+  // one slice, or of two where only one field is written (a lane's address
+  // and layer work, not the stores, then bounds a block of one slice: 160 x
+  // 144 x 96 x 20 slices 31 against 36 us, 255 x 241 x 127 x 20 119 against
+  // 153, with both fields 57 and 56, 270 and 248); or the tuning's slices
+  // per block in spans of one group (order 0) or of the rule's slices (order
+  // 1).
+  const pcsdf_tuning &tu = h->tuning;
+  const bool chosen = tu.composite_slices_per_block > 0;
+  int G = chosen ? tu.composite_slices_per_block
+                 : (out_ssq_dev && out_sdf_dev ? 1 : 2);
+  G = std::min(G, n_slices);
+  const int groups = (n_slices + G - 1) / G;
+  const bool copy16 = static_copy && !need && use_static16(h, V, groups);
+  int span = 1;
+  if (!chosen || tu.composite_order == 1)
+    span = std::max(1, (slices_per_span(V, n_slices, copy16) + G - 1) / G);
+  // gridDim.z, which also holds up to 3 parts of the octets
+  while ((groups + span - 1) / span > 65535 / 3) ++span;
   const uint32_t plane = (uint32_t)nx * (uint32_t)ny;
   const uint32_t Vu = (uint32_t)V;
-  const uintptr_t out_bits =
-      (uintptr_t)out_ssq_dev | (uintptr_t)out_sdf_dev;
-  const uint64_t N = (uint64_t)n_slices * (uint64_t)V;
-  if (V % 2 != 0 && !need && !(out_bits & 15) && N + 4 <= 0xFFFFFFFFull) {
-    // aligned packs of the flattened outputs (see k_composite_flat): for
-    // odd V they beat one voxel per lane (255x255x127 x 20: 0.39 -> 0.34
-    // ms); for V = 2 mod 4 two-voxel packs that read the static field once
-    // stay faster.  Larger outputs take the per-slice packs below.
-    launch_comp_flat(h, static_ssq_dev, P, out_ssq_dev, out_sdf_dev,
-                            plane, Vu, N, Kt, has_above, hf, s);
-    return check_launch(h, "composite");
-  }
   const int16_t *S16 = nullptr;
-  if (static_copy && !need && use_static16(h, V, (n_slices + G - 1) / G)) {
+  if (copy16) {
     // the copy lives in the static build's intermediate buffer, which is
     // free between builds
     int rc = ensure_buffer(h, h->tmp_buf, (size_t)V * 2, s);
@@ -439,26 +361,13 @@ int launch_composite(Handle *h, const pcsdf_grid *g,
     if ((rc = check_launch(h, "static16"))) return rc;
     S16 = c;
   }
-  if (ps.vec == 4 && !ps.gather)
-    launch_comp<4, false>(h, static_ssq_dev, P, need, out_ssq_dev, out_sdf_dev,
-                          plane, n_slices, G, Kt, has_above, hf, Vu, S16,
-                          s);
-  else if (ps.vec == 4)
-    launch_comp<4, true>(h, static_ssq_dev, P, need, out_ssq_dev, out_sdf_dev,
-                         plane, n_slices, G, Kt, has_above, hf, Vu, S16,
-                          s);
-  else if (ps.vec == 2 && !ps.gather)
-    launch_comp<2, false>(h, static_ssq_dev, P, need, out_ssq_dev, out_sdf_dev,
-                          plane, n_slices, G, Kt, has_above, hf, Vu, S16,
-                          s);
-  else if (ps.vec == 2)
-    launch_comp<2, true>(h, static_ssq_dev, P, need, out_ssq_dev, out_sdf_dev,
-                         plane, n_slices, G, Kt, has_above, hf, Vu, S16,
-                          s);
+  if (packs_aligned((int64_t)nx * ny, V, static_ssq_dev, out_ssq_dev,
+                    out_sdf_dev))
+    launch_comp<true>(h, static_ssq_dev, P, need, out_ssq_dev, out_sdf_dev,
+                      plane, n_slices, G, span, Kt, has_above, hf, Vu, S16, s);
   else
-    launch_comp<1, false>(h, static_ssq_dev, P, need, out_ssq_dev, out_sdf_dev,
-                          plane, n_slices, G, Kt, has_above, hf, Vu, S16,
-                          s);
+    launch_comp<false>(h, static_ssq_dev, P, need, out_ssq_dev, out_sdf_dev,
+                       plane, n_slices, G, span, Kt, has_above, hf, Vu, S16, s);
   return check_launch(h, "composite");
 }
 

@@ -17,6 +17,29 @@ __device__ __forceinline__ int32_t add_sat(int32_t a, int32_t b) {
 #endif
 }
 
+// Division of 32-bit unsigned values by a divisor known on the host, as a
+// high product, an add and two shifts (Granlund and Montgomery's round-up
+// method, exact for every 32-bit n): the compiler's division by a runtime
+// value is about 30 instructions, several of them quarter-rate.
+struct FastDiv {
+  uint32_t d = 1, m = 1;
+  uint16_t s1 = 0, s2 = 0;
+};
+inline FastDiv fast_div(uint32_t d) {
+  FastDiv f;
+  int l = 0;
+  while (l < 32 && (1ull << l) < d) ++l;
+  f.d = d;
+  f.m = (uint32_t)(((((1ull << l) - d) << 32) / d) + 1);
+  f.s1 = (uint16_t)(l < 1 ? l : 1);
+  f.s2 = (uint16_t)(l < 1 ? 0 : l - 1);
+  return f;
+}
+__device__ __forceinline__ uint32_t quotient(uint32_t n, const FastDiv &f) {
+  const uint32_t t = (uint32_t)(((uint64_t)f.m * n) >> 32);
+  return (t + ((n - t) >> f.s1)) >> f.s2;
+}
+
 // Correctly rounded square root of a float a that is 0 or at least 1 (here
 // the magnitude of an integer squared distance).  The hardware root r is
 // within one ulp for such inputs, so the rounded root is r or one of its
@@ -74,8 +97,9 @@ __device__ __forceinline__ HumanLayer human_layer(int k, int Kt,
   const int dzp = max(dz, 0);
   const int upp = max(Kt + 1 - k, 0);  // 0 above the cylinders
   HumanLayer t;
-  t.lo = has_above ? -(upp * upp) : (dz > 0 ? 0 : -INT32_MAX);
-  t.add = dzp * dzp;
+  // layers are below 2^10: the full-rate 24-bit multiplier
+  t.lo = has_above ? -__mul24(upp, upp) : (dz > 0 ? 0 : -INT32_MAX);
+  t.add = __mul24(dzp, dzp);
   return t;
 }
 __device__ __forceinline__ int32_t human_value(int32_t p, HumanLayer t) {
