@@ -77,7 +77,7 @@ inline int plan_batch(Handle *h, int n_scenes, const pcsdf_scene *scenes,
   bp->scenes.resize(n_scenes);
   bp->xy_off.resize(n_scenes);
   bp->xy.clear();
-  int lds_need = 0;
+  int64_t lds_need = 0;
   for (int q = 0; q < n_scenes; ++q) {
     const pcsdf_scene &in = scenes[q];
     const std::string tag = "scene " + std::to_string(q) + ": ";
@@ -128,9 +128,11 @@ inline int plan_batch(Handle *h, int n_scenes, const pcsdf_scene *scenes,
         bp->xy.push_back(Y);
       }
     }
-    lds_need = std::max(lds_need, d.K * 16 + d.K * d.ny * 8);
+    lds_need = std::max(
+        lds_need,
+        std::max((int64_t)d.K * 16, tile_lds(d.K, disk_rows(R, d.ny))));
   }
-  bp->lds_cap = std::min(lds_need, 48 * 1024);
+  bp->lds_cap = (int)std::min<int64_t>(lds_need, 48 * 1024);
   // composite items, counted per scene; a batch with too many of the default
   // size gets longer ones
   int64_t next = count_items(bp);
@@ -149,9 +151,8 @@ inline int plan_batch(Handle *h, int n_scenes, const pcsdf_scene *scenes,
   bp->scene_of.clear();
   for (int q = 0; q < n_scenes; ++q) {
     const SceneDev &d = bp->scenes[q];
-    const int64_t npx = (int64_t)d.nx * d.ny;
-    const int tiles = chords_in_lds(d.K, d.ny, bp->lds_cap)
-                          ? (int)((npx + kPlaneTile - 1) / kPlaneTile)
+    const int tiles = planes_tiled(d.K, d.R, d.ny, bp->lds_cap)
+                          ? plane_tiles(d.nx, d.ny)
                           : 1;
     for (int s = 0; s < d.n; ++s)
       for (int t = 0; t < tiles; ++t)

@@ -240,6 +240,7 @@ int humans_upload(Handle *h, const pcsdf_grid *g, int32_t n_slices,
     out->C.xy = xy_dev;
     out->C.Rs = xy_dev + 2 * ncent;
   }
+  out->max_R = *std::max_element(xy.begin() + 2 * ncent, xy.end());
   out->chords = reinterpret_cast<int2 *>(h->chord_buf.ptr);
   out->K = empty ? 0 : n_humans;
   out->Kt = empty ? -1 : Kt;
@@ -257,8 +258,8 @@ int planes_from(Handle *h, const pcsdf_grid *g, const HumanSet &hs,
   int32_t *p2 = reinterpret_cast<int32_t *>(h->plane_buf.ptr);
   // Planar signed field of the disk union, per slice.
   ProfScope pp(h, PCSDF_KERNEL_PLANES, s, true);
-  if ((rc = launch_planes(h, hs.C, n_humans, hs.K == 0, hs.chords, p2,
-                          nx, ny, n_slices, need, s)))
+  if ((rc = launch_planes(h, hs.C, n_humans, hs.K == 0, hs.max_R, hs.chords,
+                          p2, nx, ny, n_slices, need, s)))
     return rc;
   out->P = p2;
   out->Kt = hs.Kt;
@@ -497,8 +498,10 @@ extern "C" int pcsdf_predicted_composite_sdf_noalloc(
   const bool empty = Kt < 0 || n_humans == 0;
   int32_t *P = reinterpret_cast<int32_t *>(base);
   int2 *chords = reinterpret_cast<int2 *>(base + chord_off);
-  if ((rc = launch_planes(h, C, n_humans, empty, chords, P, nx, ny, n_slices,
-                          nullptr, s)))
+  if ((rc = launch_planes(h, C, n_humans, empty,
+                          *std::max_element(C.w + C.rs_off,
+                                            C.w + C.rs_off + n_slices),
+                          chords, P, nx, ny, n_slices, nullptr, s)))
     return rc;
   const int Kt_eff = empty ? -1 : Kt;
   return launch_composite(h, g, static_ssq_dev, P, nullptr, Kt_eff,

@@ -189,19 +189,14 @@ __device__ __forceinline__ int64_t radius_of(const Centres &c, int64_t s) {
 }
 
 // Planar signed field of the humans' disk union for every slice, into
-// P [n_slices][ny][nx]: chords per (slice, human, row) into `chords`, then
-// one lane per pixel.  C holds the fixed-point centres [n_slices][K][2]
-// and each slice's fixed-point disk radius; no human voxel at all when
-// `empty` is set.  With `need` (device int32 [n_slices]) only slices with
-// a non-zero entry are computed.
+// P [n_slices][ny][nx].  C holds the fixed-point centres [n_slices][K][2]
+// and each slice's fixed-point disk radius, max_R the largest of them; no
+// human voxel at all when `empty` is set.  `chords` [n_slices][K][ny] and the
+// second half of P [2][n_slices][ny][nx] are workspace.  With `need` (device
+// int32 [n_slices]) only slices with a non-zero entry are computed.
 int launch_planes(Handle *h, const Centres &C, int K, bool empty,
-                  int2 *chords, int32_t *P, int nx, int ny, int n_slices,
-                  const int32_t *need, hipStream_t s);
-
-// Chords only (the first step of launch_planes): chords[s][k][j], K humans
-// per slice (0: nothing to do).
-int launch_chords(Handle *h, const Centres &C, int K, int2 *chords, int nx,
-                  int ny, int n_slices, const int32_t *need, hipStream_t s);
+                  int64_t max_R, int2 *chords, int32_t *P, int nx, int ny,
+                  int n_slices, const int32_t *need, hipStream_t s);
 
 // ---- implemented in composite.hip --------------------------------------
 
@@ -211,6 +206,7 @@ int launch_chords(Handle *h, const Centres &C, int K, int2 *chords, int nx,
 // (one pinned staging copy); the chords buffer sized for them.
 struct HumanSet {
   Centres C;          // fixed-point centres and radii
+  int64_t max_R;      // largest radius of the slices
   int2 *chords;       // device, [n_slices][K][ny] (K >= 1 rows reserved)
   int K;              // humans per slice after dropping empty cylinders
   int Kt;             // highest voxel layer of the cylinders, -1 if none

@@ -9,8 +9,10 @@
 // [ceil((X-W)/2^15), floor((X+W)/2^15)].  All of this is exact integer
 // arithmetic (divisions by powers of two are arithmetic shifts).
 //
-// With the chords in hand every pixel is independent, so the plane is
-// computed one pixel per lane instead of by sequential column sweeps:
+// With the chords in hand every pixel is independent.  Most calls evaluate
+// them by tiles, chords and all in one launch (plane_tile.h).  Large stacks
+// of slices with many chords take the static build's passes, and the rest is
+// computed one pixel per lane:
 //   outside D:  E_D(i,j) = min over disks, over the disk's rows jj, of
 //               (j-jj)^2 + (distance from i to the chord)^2,
 //               pruned by each disk's bounding box and by (j-jj)^2 >= best;
@@ -23,12 +25,29 @@
 // Both are the definition of the squared distance written row by row
 // (the x term of the nearest voxel in row jj is the distance to the
 // nearest chord end), so the result is exact.
+#include <algorithm>
 #include <type_traits>
 
 #include "internal.h"
-#include "plane_device.h"
+#include "plane_tile.h"
 
 namespace pcsdf {
+
+// The tiled kernel's limits.  Disks of more rows than its coverage words
+// reach (kTileReach either side) would take its slow path, row by row from
+// the chords, at every pixel they cover; so would dense crowds, whose disks
+// join.  Against the paths below (us a call of 1000 direct queries; 51 rows
+// per disk at 512 x 512, 26 at 256 x 256):
+//   512 x 512 x 50 slices: 1, 8, 16, 32 disks 50, 107, 151, 420 against 141,
+//   213, 236, 282 by coverage and column passes;
+//   256 x 256 x 20: 3, 16, 64, 128 disks 22, 46, 112, 1245 against 39, 95,
+//   360, 774 per pixel;  512 x 512 x 2: 8, 32, 64 disks 30, 50, 505 against
+//   36, 82, 164.
+// The lines are drawn in chords per slice, disks times rows.
+constexpr int64_t kTileLds = 48 * 1024;
+constexpr int kTileMaxRows = 2 * kTileReach;
+constexpr int kTileChords = 1664;
+constexpr int kTileChordsStack = 1024;  // where the column passes apply
 
 // chords[s][k][j] = (a, b), empty when a > b.
 // Slices whose entry in `need` is zero are skipped (all slices when `need`
@@ -142,8 +161,22 @@ __global__ __launch_bounds__(kPlaneThreads) void k_planes(
   }
 }
 
-int launch_chords(Handle *h, const Centres &C, int K, int2 *chords, int nx,
-                  int ny, int n_slices, const int32_t *need, hipStream_t s) {
+// Tile blockIdx.x of slice blockIdx.y (+ 65535 blockIdx.z).
+__global__ __launch_bounds__(64 * kTileWaves) void k_plane_tiles(
+    Centres C, int K, int rows, int nx, int ny, int n_slices,
+    const int32_t *__restrict__ need, int32_t *__restrict__ P) {
+  extern __shared__ int4 sh4[];
+  const int s = blockIdx.z * 65535 + blockIdx.y;
+  if (s >= n_slices || (need && need[s] == 0)) return;  // uniform
+  const int64_t at = 2 * (int64_t)s * K;
+  plane_tile(sh4, K, rows, radius_of(C, s), nx, ny, blockIdx.x,
+             [&](int q) { return centre_word(C, at + q); },
+             P + (int64_t)s * nx * ny);
+}
+
+static int launch_chords(Handle *h, const Centres &C, int K, int2 *chords,
+                         int nx, int ny, int n_slices, const int32_t *need,
+                         hipStream_t s) {
   const int64_t total = (int64_t)n_slices * K * ny;
   if (total <= 0) return PCSDF_OK;
   launch_timed(h, k_chords, dim3((unsigned)((total + 255) / 256)), dim3(256),
@@ -152,27 +185,40 @@ int launch_chords(Handle *h, const Centres &C, int K, int2 *chords, int nx,
 }
 
 int launch_planes(Handle *h, const Centres &C, int K, bool empty,
-                  int2 *chords, int32_t *P, int nx, int ny, int n_slices,
-                  const int32_t *need, hipStream_t s) {
+                  int64_t max_R, int2 *chords, int32_t *P, int nx, int ny,
+                  int n_slices, const int32_t *need, hipStream_t s) {
   const int Keff = empty ? 0 : K;
+  const int rows = disk_rows(max_R, ny);
+  const int64_t lds = tile_lds(Keff, rows);
+  // a stack with a workgroup of column segments (64 columns of a slice) per
+  // CU, in columns whose envelopes stay in LDS (16-bit entries)
+  const bool stack = !need && Keff > 0 && ny <= 512 &&
+                     h->tuning.static_segments == 0 &&
+                     (int64_t)((nx + 63) / 64) * n_slices >= 256;
+  if (nx <= kTilePlaneMax && ny <= kTilePlaneMax && rows <= kTileMaxRows &&
+      (int64_t)Keff * rows <= (stack ? kTileChordsStack : kTileChords) &&
+      lds <= kTileLds) {
+    launch_timed(h, k_plane_tiles,
+                 dim3((unsigned)plane_tiles(nx, ny),
+                      (unsigned)std::min(n_slices, 65535),
+                      (unsigned)((n_slices + 65534) / 65535)),
+                 dim3(64 * kTileWaves), (uint32_t)lds, s, C, Keff, rows, nx,
+                 ny, n_slices, need, P);
+    return check_launch(h, "plane_tiles");
+  }
   int rc0 = launch_chords(h, C, Keff, chords, nx, ny, n_slices, need, s);
   if (rc0) return rc0;
   const int npx = nx * ny;
   int32_t *F1 = P + (int64_t)n_slices * npx;
   const int64_t npix = (int64_t)n_slices * npx;
-  if (!need && Keff > 0 && ny <= 512 && h->tuning.static_segments == 0 &&
-      (int64_t)((nx + 63) / 64) * n_slices >= 256) {
+  if (stack) {
     // Every slice of a large stack: the planar field is the 2-D signed EDT
     // of the disks' coverage, by the static build's row pass and y column
     // pass over the stack of slices (each slice a z layer of an
     // nx x ny x n grid).  The coverage bytes use the front of P, the row
     // pass's output the back.  With the default segment counts (a static
-    // build tuning sends the planes to the per-pixel kernel) columns of at
-    // most 512 pixels keep the column pass's envelopes in LDS (16-bit
-    // entries), so no workspace is allocated.  Below one workgroup of
-    // column segments per CU (64 columns of a slice each) the per-pixel
-    // kernel is faster (512 x 512 x 50 slices: 0.20 ms against 0.47;
-    // 256 x 256 x 20: 0.076 against 0.035).
+    // build tuning sends the planes to the per-pixel kernel) no workspace
+    // is allocated.
     uint8_t *cov = reinterpret_cast<uint8_t *>(P);
     launch_timed(h, k_cover, dim3((unsigned)(npix / nx)), dim3(256), 0u, s,
                  chords, Keff, nx, ny, cov);

@@ -193,7 +193,7 @@ extern "C" int pcsdf_template_composite_sdf(
       Centres C;
       C.xy = dev;
       C.Rs = dev + 2 * K;
-      if ((rc = launch_planes(h, C, 1, false,
+      if ((rc = launch_planes(h, C, 1, false, R,
                               reinterpret_cast<int2 *>(h->chord_buf.ptr), T,
                               Wx, Wy, K, nullptr, s)))
         return rc;
