@@ -32,13 +32,21 @@
 //     so the envelope has no division.  Columns too long for the segmented
 //     kernel's LDS run both channels in one wave per 32 columns
 //     (k_pass_col), and passes with few columns one lane per voxel
-//     (k_pass_col_search).
+//     (k_pass_col_search).  Large volumes in which every voxel has one of
+//     the other type near propagate both channels along the columns in
+//     registers instead (edt_prop.h).
 #include "device_common.h"
 #include "internal.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace pcsdf {
+
+// What a static build finds out on the device with its x pass (edt_prop.h).
+struct EdtPlan {
+  int32_t near;  // whether every voxel's distance is known to be small
+};
 
 // ------------------------------------------------------------------ x pass
 
@@ -139,20 +147,19 @@ struct BytePack<16> {
   typedef uint4 T;
 };
 
+constexpr int kNone = 0x40000000;
+
+// One row, given its occupancy: d[j] is the distance of voxel i0 + j to the
+// nearest voxel of the other type (kNone or more: there is none), bit j of
+// *occupied its type; *lanes_occ and *lanes_free: the lanes that hold a
+// voxel of either.
 template <int VPL>
-__global__ __launch_bounds__(256) void k_pass_x_vec(const uint8_t *occ,
-                                                    int32_t *out, int nx,
-                                                    int64_t rows) {
-  const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= rows) return;  // uniform across the wave
-  constexpr int kNone = 0x40000000;
+__device__ __forceinline__ void x_row(typename BytePack<VPL>::T raw, int nx,
+                                      int lane, int (&d)[VPL],
+                                      uint32_t *occupied, uint64_t *lanes_occ,
+                                      uint64_t *lanes_free) {
   const int i0 = lane * VPL;
   const bool valid = i0 < nx;  // the whole pack: nx is a multiple of VPL
-  typename BytePack<VPL>::T raw{};
-  if (valid)
-    raw = *reinterpret_cast<const typename BytePack<VPL>::T *>(
-        occ + row * nx + i0);
   const uint8_t *bytes = reinterpret_cast<const uint8_t *>(&raw);
   uint32_t mo = 0;  // bit j: voxel i0 + j is occupied
 #pragma unroll
@@ -164,6 +171,9 @@ __global__ __launch_bounds__(256) void k_pass_x_vec(const uint8_t *occ,
   const int firstO = mo ? i0 + __builtin_ctz(mo) : kNone;
   const int firstF = mf ? i0 + __builtin_ctz(mf) : kNone;
   const uint64_t anyO = __ballot(mo != 0), anyF = __ballot(mf != 0);
+  *occupied = mo;
+  *lanes_occ = anyO;
+  *lanes_free = anyF;
   const uint64_t below = (1ull << lane) - 1ull;
   const uint64_t above = lane == 63 ? 0ull : ~0ull << (lane + 1);
   const uint64_t bO = anyO & below, bF = anyF & below;
@@ -187,7 +197,6 @@ __global__ __launch_bounds__(256) void k_pass_x_vec(const uint8_t *occ,
     else
       lF = i0 + j;
   }
-  int32_t v[VPL];
 #pragma unroll
   for (int j = VPL - 1; j >= 0; --j) {
     const bool o = (mo >> j) & 1u;
@@ -198,24 +207,55 @@ __global__ __launch_bounds__(256) void k_pass_x_vec(const uint8_t *occ,
     else
       rF = i;
     const int l = left[j];
-    const bool none_l = l < 0, none_r = r >= nx;
-    int32_t d2;
-    if (none_l && none_r) {
-      d2 = kInf;
-    } else {
-      const int dl = none_l ? kNone : i - l;
-      const int dr = none_r ? kNone : r - i;
-      const int d = dl < dr ? dl : dr;
-      d2 = d * d;
-    }
-    v[j] = o ? -d2 : d2;
+    d[j] = min(l < 0 ? kNone : i - l, r >= nx ? kNone : r - i);
   }
-  if (valid) {
+}
+
+template <int VPL>
+__device__ __forceinline__ typename BytePack<VPL>::T x_load(const uint8_t *row,
+                                                            int nx, int lane) {
+  typename BytePack<VPL>::T raw{};
+  if (lane * VPL < nx)
+    raw = *reinterpret_cast<const typename BytePack<VPL>::T *>(row +
+                                                               lane * VPL);
+  return raw;
+}
+
+template <int VPL>
+__global__ __launch_bounds__(256) void k_pass_x_vec(const uint8_t *occ,
+                                                    int32_t *out, int nx,
+                                                    int64_t rows) {
+  const int lane = threadIdx.x & 63;
+  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (row >= rows) return;  // uniform across the wave
+  int d[VPL];
+  uint32_t mo;
+  uint64_t lo, lf;
+  x_row<VPL>(x_load<VPL>(occ + row * nx, nx, lane), nx, lane, d, &mo, &lo,
+             &lf);
+  int32_t v[VPL];
+#pragma unroll
+  for (int j = 0; j < VPL; ++j) {
+    const int32_t d2 = d[j] >= kNone ? kInf : d[j] * d[j];
+    v[j] = (mo >> j) & 1u ? -d2 : d2;
+  }
+  const int i0 = lane * VPL;
+  if (i0 < nx) {
     int4 *dst = reinterpret_cast<int4 *>(out + row * nx + i0);
 #pragma unroll
     for (int c = 0; c < VPL / 4; ++c)
       dst[c] = make_int4(v[4 * c], v[4 * c + 1], v[4 * c + 2], v[4 * c + 3]);
   }
+}
+
+// VPL voxels per lane where the row fits one wave and every pack is aligned
+// (occupancy to VPL bytes, values to 16), else 0.
+static int voxels_per_lane(const uint8_t *occ, const int32_t *out, int nx) {
+  for (int c : {4, 8, 16})
+    if (nx <= 64 * c && nx % c == 0 && !((uintptr_t)occ % c) &&
+        !((uintptr_t)out % 16))
+      return c;
+  return 0;
 }
 
 template <class Occ>
@@ -244,15 +284,7 @@ static int launch_x(Handle *h, const Occ &occ, int32_t *out, int nx,
 
 int launch_pass_x_u8(Handle *h, const uint8_t *occ, int32_t *out, int nx,
                      int64_t rows, hipStream_t s) {
-  // VPL voxels per lane where the row fits one wave and every pack is
-  // aligned (occupancy to VPL bytes, values to 16)
-  int vpl = 0;
-  for (int c : {4, 8, 16})
-    if (nx <= 64 * c && nx % c == 0 && !((uintptr_t)occ % c) &&
-        !((uintptr_t)out % 16)) {
-      vpl = c;
-      break;
-    }
+  const int vpl = voxels_per_lane(occ, out, nx);
   if (vpl == 0 || rows <= 0)
     return launch_x(h, OccU8{occ, nx}, out, nx, rows, s, "pass_x_u8");
   const dim3 grid((unsigned)((rows + 3) / 4)), block(256);
@@ -411,6 +443,15 @@ __global__ __launch_bounds__(64) void k_pass_col(
 // stack test.
 constexpr int kSegBatch = 16;
 
+// A launch with a plan, and one without (nothing is near).
+struct Planned {
+  const EdtPlan *p;
+  __device__ __forceinline__ bool near() const { return p->near != 0; }
+};
+struct Unplanned {
+  __device__ __forceinline__ bool near() const { return false; }
+};
+
 // The low 24 bits, sign-extended: marks a value as fitting the 24-bit
 // multiplier, which reads only those bits (the extension costs nothing).
 // mul24 is the product of two such values on that multiplier, mul48 its
@@ -465,6 +506,19 @@ struct EnvLds {
   static constexpr int bytes() { return kRoot ? 2 : 4; }
 };
 
+// An element of a partial field: a signed square, or (16-bit) a signed
+// distance.  +-no_site: there is no voxel of the other type.
+constexpr int kNoDist = INT16_MAX;
+template <class T>
+__device__ constexpr T no_site() {
+  return sizeof(T) == 2 ? (T)kNoDist : (T)kInf;
+}
+// the square of a non-negative element
+template <class T>
+__device__ __forceinline__ int32_t square_of(int32_t v) {
+  return sizeof(T) == 2 ? mul24(v, v) : v;
+}
+
 // Square root of a perfect square below 2^20: the hardware's approximate
 // root is within an ulp (2^-13 here) of the integer, so rounding to
 // nearest recovers it exactly.
@@ -472,12 +526,15 @@ __device__ __forceinline__ int root_of_square(int f) {
   return (int)(__builtin_amdgcn_sqrtf((float)f) + 0.5f);
 }
 
-template <int S, bool kWriteSdf, bool kRoot>
+// (With a plan that found all near there is nothing to do: k_pass_col_prop
+// has done the pass.)
+template <int S, bool kWriteSdf, bool kRoot, class T, class Plan>
 __global__ __launch_bounds__(64 * S) void k_pass_col_seg(
-    const int32_t *__restrict__ in, int32_t *__restrict__ out,
+    const T *__restrict__ in, int32_t *__restrict__ out,
     float *__restrict__ sdf, float hf, int nfast, int m, int64_t stride,
-    int64_t outer_stride, int64_t nblocks, int tiles) {
+    int64_t outer_stride, int64_t nblocks, int tiles, Plan plan) {
   extern __shared__ uint32_t lds_seg[];
+  if (plan.near()) return;
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int L = (m + S - 1) / S;
@@ -494,7 +551,7 @@ __global__ __launch_bounds__(64 * S) void k_pass_col_seg(
     const int i = tile * 64 + lane;
     const bool active = i < nfast;
     const int64_t at0 = o * outer_stride + (active ? i : 0) + q0 * stride;
-    const int32_t *src = in + at0;  // row q0 of this lane's column
+    const T *src = in + at0;  // row q0 of this lane's column
     int32_t *dst = out + at0;
     float *dsdf = kWriteSdf ? sdf + at0 : nullptr;
 
@@ -506,18 +563,18 @@ __global__ __launch_bounds__(64 * S) void k_pass_col_seg(
     int pb = 0, hb = 0;  // entry top - 1
     int pc = 0, hc = 0;  // entry top - 2
     for (int qb = q0; qb < q1; qb += kSegBatch) {
-      int32_t xb[kSegBatch];
+      T xb[kSegBatch];
 #pragma unroll
       for (int t = 0; t < kSegBatch; ++t)
         xb[t] = (active && qb + t < q1)
                     ? src[(int64_t)(qb - q0 + t) * stride]
-                    : kInf;
+                    : no_site<T>();
 #pragma unroll
       for (int t = 0; t < kSegBatch; ++t) {
         const int q = qb + t;
-        const int32_t x = xb[t];
-        if (x == kInf) continue;  // no site in this row (or past the end)
-        const int f = x > 0 ? x : 0;
+        const T x = xb[t];
+        if (x == no_site<T>()) continue;  // in this row (or past the end)
+        const int r = max((int)x, 0), f = square_of<T>(r);
         const int hq = f + mul24(q, q);
         while (top >= 1) {
           // The top stays if the new parabola overtakes it to the right
@@ -537,7 +594,8 @@ __global__ __launch_bounds__(64 * S) void k_pass_col_seg(
         pa = q;
         ha = hq;
         ++top;
-        env.put(w, top, lane, q, hq, kRoot ? root_of_square(f) : 0);
+        env.put(w, top, lane, q, hq,
+                kRoot ? (sizeof(T) == 2 ? r : root_of_square(f)) : 0);
       }
     }
     tops[w * 64 + lane] = top;
@@ -703,40 +761,42 @@ __global__ __launch_bounds__(256) void k_pass_col_search(
 // farther rows are farther still).  Neighbouring rows share their
 // neighbours, so a group costs about one search instead of G.  Exact, like
 // the envelope.  Grid: (lanes of one outer index / 256, outer indices).
-template <bool kWriteSdf, int G>
+template <bool kWriteSdf, int G, class T, class Plan>
 __global__ __launch_bounds__(256) void k_pass_col_inside(
-    const int32_t *__restrict__ in, int32_t *__restrict__ out,
+    const T *__restrict__ in, int32_t *__restrict__ out,
     float *__restrict__ sdf, float hf, int nfast, int m, int64_t stride,
-    int64_t outer_stride) {
+    int64_t outer_stride, Plan plan) {
+  if (plan.near()) return;
   const uint32_t mg = (uint32_t)(m + G - 1) / G;
   const uint32_t t = blockIdx.x * 256u + threadIdx.x;
   if (t >= (uint32_t)nfast * mg) return;
   const int qg = (int)(t / (uint32_t)nfast);
   const int i = (int)(t - (uint32_t)qg * (uint32_t)nfast);
   // The outer index's slab is uniform across the block, so each access is
-  // a uniform base plus a 32-bit lane byte offset (a slab holds at most
-  // 2^30 elements).
+  // a uniform base plus a 32-bit lane offset (a slab holds at most 2^30
+  // elements).
   const int64_t o = blockIdx.y;
   const char *base = reinterpret_cast<const char *>(in + o * outer_stride);
   char *obase = reinterpret_cast<char *>(out + o * outer_stride);
   char *fbase = kWriteSdf ? reinterpret_cast<char *>(sdf + o * outer_stride)
                           : nullptr;
-  const uint32_t st = (uint32_t)stride * 4u;  // bytes
-  auto ld = [&](uint32_t off) -> int32_t {
-    return *reinterpret_cast<const int32_t *>(base + off);
+  const uint32_t st = (uint32_t)stride;
+  constexpr T kOut = -no_site<T>();
+  auto ld = [&](uint32_t off) -> T {
+    return *reinterpret_cast<const T *>(base + off * (uint32_t)sizeof(T));
   };
   // value of a row in the free set's channel: 0 on a free voxel, f_F on an
   // occupied one, kInf where the row has no free voxel (rows outside the
-  // column are passed as -kInf)
-  auto f_free = [](int32_t v) -> int32_t {
-    return v == -kInf ? kInf : (v < 0 ? -v : 0);
+  // column are passed as kOut)
+  auto f_free = [](T v) -> int32_t {
+    return v == kOut ? kInf : square_of<T>(max(-(int32_t)v, 0));
   };
   const int qa = qg * G;
   const int n = min(G, m - qa);  // rows of the group inside the column
-  const uint32_t at0 = (uint32_t)i * 4u + (uint32_t)qa * st;
-  int32_t x[G];
+  const uint32_t at0 = (uint32_t)i + (uint32_t)qa * st;
+  T x[G];
 #pragma unroll
-  for (int r = 0; r < G; ++r) x[r] = r < n ? ld(at0 + (uint32_t)r * st) : -kInf;
+  for (int r = 0; r < G; ++r) x[r] = r < n ? ld(at0 + (uint32_t)r * st) : kOut;
   bool need[G];  // occupied rows: the ones this channel writes
   bool any = false;
 #pragma unroll
@@ -767,14 +827,14 @@ __global__ __launch_bounds__(256) void k_pass_col_inside(
     lo = lo && qa - d0 >= 0;
     hi = hi && qa + n - 1 + d0 < m;
     if (!lo && !hi) break;
-    int32_t vl[kSearchBatch], vh[kSearchBatch];
+    T vl[kSearchBatch], vh[kSearchBatch];
 #pragma unroll
     for (int u = 0; u < kSearchBatch; ++u) {
       const int d = d0 + u;
-      vl[u] = lo && qa - d >= 0 ? ld(at0 - (uint32_t)d * st) : -kInf;
+      vl[u] = lo && qa - d >= 0 ? ld(at0 - (uint32_t)d * st) : kOut;
       vh[u] = hi && qa + n - 1 + d < m
                   ? ld(at0 + (uint32_t)(n - 1 + d) * st)
-                  : -kInf;
+                  : kOut;
     }
 #pragma unroll
     for (int u = 0; u < kSearchBatch; ++u) {
@@ -792,7 +852,7 @@ __global__ __launch_bounds__(256) void k_pass_col_inside(
   for (int r = 0; r < G; ++r) {
     if (!need[r]) continue;
     const int32_t v = best[r] == kInf ? -kInf : -best[r];
-    const uint32_t at = at0 + (uint32_t)r * st;
+    const uint32_t at = (at0 + (uint32_t)r * st) * 4u;
     *reinterpret_cast<int32_t *>(obase + at) = v;
     if (kWriteSdf)
       *reinterpret_cast<float *>(fbase + at) = ssq_to_metres(v, hf);
@@ -816,51 +876,35 @@ static hipError_t allow_lds(const void *kernel, size_t bytes) {
                              (int)bytes);
 }
 
-template <int S, bool kRoot>
-static hipError_t launch_seg(Handle *h, const int32_t *in, int32_t *out,
-                             float *sdf_out,
-                             float h_f, int nfast, int m, int64_t stride,
-                             int64_t outer_stride, int64_t nblocks, int tiles,
-                             size_t lds, hipStream_t s) {
+template <bool kRoot, class T, class Plan>
+static int launch_seg(Handle *h, int S, const T *in, int32_t *out,
+                      float *sdf_out, float h_f, int nfast, int nouter, int m,
+                      int64_t stride, int64_t outer_stride, Plan plan,
+                      size_t lds, hipStream_t s) {
+  const int tiles = (nfast + 63) / 64;
+  const int64_t nblocks = (int64_t)tiles * nouter;
   const unsigned grid =
       (unsigned)(nblocks < (1LL << 30) ? nblocks : (1LL << 30));
-  if (sdf_out) {
-    const hipError_t e = allow_lds(
-        reinterpret_cast<const void *>(&k_pass_col_seg<S, true, kRoot>),
-        lds);
-    if (e != hipSuccess) return e;
-    launch_timed(h, k_pass_col_seg<S, true, kRoot>, dim3(grid),
-                       dim3(64 * S), lds, s, in, out, sdf_out, h_f, nfast, m,
-                       stride, outer_stride, nblocks, tiles);
-  } else {
-    const hipError_t e = allow_lds(
-        reinterpret_cast<const void *>(&k_pass_col_seg<S, false, kRoot>),
-        lds);
-    if (e != hipSuccess) return e;
-    launch_timed(h, k_pass_col_seg<S, false, kRoot>, dim3(grid),
-                       dim3(64 * S), lds, s, in, out, sdf_out, h_f, nfast, m,
-                       stride, outer_stride, nblocks, tiles);
-  }
-  return hipSuccess;
-}
-
-template <bool kRoot>
-static hipError_t launch_seg_any(Handle *h, int S, const int32_t *in,
-                                 int32_t *out,
-                                 float *sdf_out, float h_f, int nfast, int m,
-                                 int64_t stride, int64_t outer_stride,
-                                 int64_t nblocks, int tiles, size_t lds,
-                                 hipStream_t s) {
+  auto go = [&](auto kernel) -> int {
+    const hipError_t e = allow_lds(reinterpret_cast<const void *>(kernel), lds);
+    if (e != hipSuccess)
+      return fail(h, PCSDF_ERR_HIP,
+                  std::string("raising the LDS limit of pass_col_seg: ") +
+                      hipGetErrorString(e));
+    launch_timed(h, kernel, dim3(grid), dim3(64 * S), lds, s, in, out, sdf_out,
+                 h_f, nfast, m, stride, outer_stride, nblocks, tiles, plan);
+    return check_launch(h, "pass_col_seg");
+  };
   switch (S) {
     case 2:
-      return launch_seg<2, kRoot>(h, in, out, sdf_out, h_f, nfast, m, stride,
-                                  outer_stride, nblocks, tiles, lds, s);
+      return sdf_out ? go(&k_pass_col_seg<2, true, kRoot, T, Plan>)
+                     : go(&k_pass_col_seg<2, false, kRoot, T, Plan>);
     case 4:
-      return launch_seg<4, kRoot>(h, in, out, sdf_out, h_f, nfast, m, stride,
-                                  outer_stride, nblocks, tiles, lds, s);
+      return sdf_out ? go(&k_pass_col_seg<4, true, kRoot, T, Plan>)
+                     : go(&k_pass_col_seg<4, false, kRoot, T, Plan>);
     default:
-      return launch_seg<8, kRoot>(h, in, out, sdf_out, h_f, nfast, m, stride,
-                                  outer_stride, nblocks, tiles, lds, s);
+      return sdf_out ? go(&k_pass_col_seg<8, true, kRoot, T, Plan>)
+                     : go(&k_pass_col_seg<8, false, kRoot, T, Plan>);
   }
 }
 
@@ -888,6 +932,61 @@ static int column_segments(const Handle *h, int m) {
   return m >= 256 ? 8 : m >= 128 ? 4 : m >= 64 ? 2 : 1;
 }
 
+// Both channels of a pass by segments.  The free set's channel of the
+// occupied voxels by search, on the side stream (use_side), beside the
+// occupied set's channel by envelopes (64 columns per wave) on the caller's:
+// they read the same input and write disjoint voxels, and the search's
+// memory waits fill the envelope kernel's issue gaps.  Without use_side both
+// run on the caller's stream, one after the other.  `first` launches what
+// goes before the envelopes on the caller's stream.
+template <bool kRoot, class T, class Plan, class First>
+static int launch_both(Handle *h, int S, const T *in, int32_t *out,
+                       float *sdf_out, float h_f, int nfast, int nouter,
+                       int m, int64_t stride, int64_t outer_stride,
+                       bool use_side, Plan plan, size_t lds, hipStream_t s,
+                       First first) {
+  hipStream_t ss = s;
+  int rc = PCSDF_OK;
+  hipError_t e = hipSuccess;
+  if (use_side) {
+    if ((rc = ensure_side_stream(h))) return rc;
+    e = hipEventRecord(h->fork_ev, s);
+    if (e == hipSuccess) e = hipStreamWaitEvent(h->side, h->fork_ev, 0);
+    if (e != hipSuccess)
+      return fail(h, PCSDF_ERR_HIP,
+                  std::string("forking the side stream: ") +
+                      hipGetErrorString(e));
+    ss = h->side;
+  }
+  const int64_t groups =
+      (int64_t)nfast * ((m + kInsideRows - 1) / kInsideRows);
+  const dim3 grid((unsigned)((groups + 255) / 256), (unsigned)nouter);
+  if (sdf_out)
+    launch_timed(h, k_pass_col_inside<true, kInsideRows, T, Plan>, grid,
+                 dim3(256), 0, ss, in, out, sdf_out, h_f, nfast, m, stride,
+                 outer_stride, plan);
+  else
+    launch_timed(h, k_pass_col_inside<false, kInsideRows, T, Plan>, grid,
+                 dim3(256), 0, ss, in, out, sdf_out, h_f, nfast, m, stride,
+                 outer_stride, plan);
+  rc = check_launch(h, "pass_col_inside");
+  if (!rc) rc = first();
+  if (!rc)
+    rc = launch_seg<kRoot>(h, S, in, out, sdf_out, h_f, nfast, nouter, m,
+                           stride, outer_stride, plan, lds, s);
+  if (!use_side) return rc;
+  // join in every case, so that no work of this call outlives it on the
+  // side stream
+  e = hipEventRecord(h->join_ev, h->side);
+  if (e == hipSuccess) e = hipStreamWaitEvent(s, h->join_ev, 0);
+  if (rc) return rc;
+  if (e != hipSuccess)
+    return fail(h, PCSDF_ERR_HIP,
+                std::string("joining the side stream: ") +
+                    hipGetErrorString(e));
+  return PCSDF_OK;
+}
+
 int launch_pass_col(Handle *h, const int32_t *in, int32_t *out,
                     float *sdf_out, float h_f, int nfast, int nouter, int m,
                     int64_t stride, int64_t outer_stride, bool square_input,
@@ -912,6 +1011,7 @@ int launch_pass_col(Handle *h, const int32_t *in, int32_t *out,
                          stride, outer_stride);
     return check_launch(h, "pass_col_search");
   }
+  auto none = [] { return PCSDF_OK; };
   int S = column_segments(h, m);
   while (S > 1 && S > m) S >>= 1;  // a power of two, at most m
   if (S > 1) {
@@ -922,61 +1022,13 @@ int launch_pass_col(Handle *h, const int32_t *in, int32_t *out,
     const size_t lds_seg =
         (size_t)S * L * 64 * (root ? 2 : 4) + (size_t)S * 64 * 4;
     if ((int64_t)lds_seg <= h->max_lds) {
-      // The free set's channel of the occupied voxels by search, on the
-      // side stream (use_side), beside the occupied set's channel by
-      // envelopes (64 columns per wave) on the caller's: they read the same
-      // input and write disjoint voxels, and the search's memory waits
-      // fill the envelope kernel's issue gaps.  Without use_side both run
-      // on the caller's stream, one after the other.
-      hipStream_t ss = s;
-      int rc = PCSDF_OK;
-      hipError_t e = hipSuccess;
-      if (use_side) {
-        if ((rc = ensure_side_stream(h))) return rc;
-        e = hipEventRecord(h->fork_ev, s);
-        if (e == hipSuccess) e = hipStreamWaitEvent(h->side, h->fork_ev, 0);
-        if (e != hipSuccess)
-          return fail(h, PCSDF_ERR_HIP,
-                      std::string("forking the side stream: ") +
-                          hipGetErrorString(e));
-        ss = h->side;
-      }
-      if (sdf_out)
-        launch_timed(h, k_pass_col_inside<true, kInsideRows>,
-                     sgrid(kInsideRows), dim3(256), 0, ss, in, out, sdf_out,
-                     h_f, nfast, m, stride, outer_stride);
-      else
-        launch_timed(h, k_pass_col_inside<false, kInsideRows>,
-                     sgrid(kInsideRows), dim3(256), 0, ss, in, out, sdf_out,
-                     h_f, nfast, m, stride, outer_stride);
-      rc = check_launch(h, "pass_col_inside");
-      if (!rc) {
-        const int tiles64 = (nfast + 63) / 64;
-        const int64_t nblocks64 = (int64_t)tiles64 * nouter;
-        e = root ? launch_seg_any<true>(h, S, in, out, sdf_out, h_f, nfast, m,
-                                        stride, outer_stride, nblocks64,
-                                        tiles64, lds_seg, s)
-                 : launch_seg_any<false>(h, S, in, out, sdf_out, h_f, nfast, m,
-                                         stride, outer_stride, nblocks64,
-                                         tiles64, lds_seg, s);
-        if (e != hipSuccess)
-          rc = fail(h, PCSDF_ERR_HIP,
-                    std::string("raising the LDS limit of pass_col_seg: ") +
-                        hipGetErrorString(e));
-        else
-          rc = check_launch(h, "pass_col_seg");
-      }
-      if (!use_side) return rc;
-      // join in every case, so that no work of this call outlives it on
-      // the side stream
-      e = hipEventRecord(h->join_ev, h->side);
-      if (e == hipSuccess) e = hipStreamWaitEvent(s, h->join_ev, 0);
-      if (rc) return rc;
-      if (e != hipSuccess)
-        return fail(h, PCSDF_ERR_HIP,
-                    std::string("joining the side stream: ") +
-                        hipGetErrorString(e));
-      return PCSDF_OK;
+      return root ? launch_both<true>(h, S, in, out, sdf_out, h_f, nfast,
+                                      nouter, m, stride, outer_stride,
+                                      use_side, Unplanned{}, lds_seg, s, none)
+                  : launch_both<false>(h, S, in, out, sdf_out, h_f, nfast,
+                                       nouter, m, stride, outer_stride,
+                                       use_side, Unplanned{}, lds_seg, s,
+                                       none);
     }
   }
   const size_t lds = (size_t)m * 64 * sizeof(uint32_t);
@@ -1019,6 +1071,117 @@ int launch_pass_col(Handle *h, const int32_t *in, int32_t *out,
   return check_launch(h, "pass_col_global_stack");
 }
 
+}  // namespace pcsdf
+
+#include "edt_prop.h"
+
+namespace pcsdf {
+
+// ---------------------------------------------- static build, large volumes
+
+// Voxels from which a build looks whether all is near (edt_prop.h).  A build
+// in which all is near gains at any size measured (256 x 512 x 256, 300 boxes:
+// 528 -> 288 us; 512 x 512 x 256, 200 boxes of 10-80 voxels: 1227 -> 564 us);
+// one in which it is not pays about 20 us for k_reach and the launches that
+// return at once, and gets back what the 16-bit distances save the x and y
+// passes: 514 -> 527 us at 41 M voxels, 604 -> 609 at 51 M, 1018 -> 998 at 67 M.
+// The line is where that is even.
+constexpr int64_t kPlanVoxels = 7LL << 23;
+
+// Blocks along an axis of n voxels; 128-column tiles of nx.
+static int coarse(int n) { return (n + kCoarse - 1) / kCoarse; }
+static int prop_tiles(int nx) { return (nx + kPropCols - 1) / kPropCols; }
+
+// A build's scratch: the intermediate field (before it is written, the
+// coarse bits), the plan, the bounds [prop_tiles][coarse z][coarse y].
+static size_t plan_offset(int64_t V) { return align_up((size_t)V * 4, 64); }
+static size_t plan_bytes(int nx, int ny, int nz) {
+  return 64 + (size_t)prop_tiles(nx) * coarse(ny) * coarse(nz) * 4;
+}
+
+static bool plan_pays(const Handle *h, int vpl, int nx, int ny, int nz) {
+  if (h->tuning.static_segments != 0 || vpl == 0 ||
+      (int64_t)nx * ny * nz < kPlanVoxels)
+    return false;
+  for (int m : {ny, nz})
+    if (m < 2 || m > kPropRows * kPropWaves ||
+        (m + 16) * 256 > h->max_lds)  // k_pass_col_seg's
+      return false;
+  return true;
+}
+
+// A column pass by the plan: k_pass_col_prop where all is near, the search
+// and the envelopes where not; all are launched, and return at once where
+// not meant.
+template <bool kLast, bool kSdf>
+static int launch_pass_planned(Handle *h, const int32_t *in, int32_t *out,
+                               float *sdf, float hf, int nfast, int nouter,
+                               int m, int64_t stride, int64_t outer_stride,
+                               int cy, int cz, const int32_t *bound,
+                               const EdtPlan *plan, hipStream_t s) {
+  const int S = std::max(2, column_segments(h, m));
+  const int L = (m + S - 1) / S;
+  constexpr bool kRoot = !kLast;  // the x pass's squares, and L <= 64
+  typedef typename std::conditional<kLast, int32_t, int16_t>::type T;
+  const size_t lds =
+      (size_t)S * L * 64 * EnvLds<kRoot>::bytes() + (size_t)S * 64 * 4;
+  return launch_both<kRoot>(
+      h, S, reinterpret_cast<const T *>(in), out, sdf, hf, nfast, nouter, m,
+      stride, outer_stride, true, Planned{plan}, lds, s, [&]() -> int {
+        const int tiles = prop_tiles(nfast);
+        const int waves = (m + kPropRows - 1) / kPropRows;
+        launch_timed(h, k_pass_col_prop<!kLast, kLast, kSdf>,
+                     dim3((unsigned)((int64_t)tiles * nouter)),
+                     dim3(64 * waves), (size_t)prop_lds(waves), s,
+                     (const void *)in, (void *)out, sdf, hf, nfast, m, stride,
+                     outer_stride, tiles, cy, cz, bound, plan);
+        return check_launch(h, "pass_col_prop");
+      });
+}
+
+static int build_planned(Handle *h, const pcsdf_grid *g, int vpl,
+                         const uint8_t *occ, int32_t *ssq, float *sdf,
+                         hipStream_t s) {
+  const int nx = g->nx, ny = g->ny, nz = g->nz;
+  const int64_t V = (int64_t)nx * ny * nz, layer = (int64_t)nx * ny;
+  const float hf = (float)g->voxel_m;
+  int32_t *tmp = reinterpret_cast<int32_t *>(h->tmp_buf.ptr);
+  char *const behind = static_cast<char *>(h->tmp_buf.ptr) + plan_offset(V);
+  EdtPlan *plan = reinterpret_cast<EdtPlan *>(behind);
+  int32_t *bound = reinterpret_cast<int32_t *>(behind + 64);
+  const int cy = coarse(ny), cz = coarse(nz);  // cy cz <= 1024
+  uint64_t *occ_bits = reinterpret_cast<uint64_t *>(tmp);
+  const int cq = (nz + kXLayers - 1) / kXLayers;
+  uint64_t *free_bits = occ_bits + cy * cq;
+  int16_t *dist = reinterpret_cast<int16_t *>(ssq);  // as scratch
+  auto x_pass = [&](auto kernel) {
+    launch_timed(h, kernel, dim3((unsigned)(cy * cq)), dim3(64 * kXLayers),
+                 0, s, occ, dist, nx, ny, nz, cy, occ_bits, free_bits);
+  };
+  if (vpl == 4)
+    x_pass(&k_pass_x_coarse<4>);
+  else if (vpl == 8)
+    x_pass(&k_pass_x_coarse<8>);
+  else
+    x_pass(&k_pass_x_coarse<16>);
+  int rc = check_launch(h, "pass_x_coarse");
+  if (rc) return rc;
+  launch_timed(h, k_reach, dim3(1), dim3((cy * cz + 63) / 64 * 64), 0, s,
+               (const uint64_t *)occ_bits, (const uint64_t *)free_bits, vpl,
+               cy, cz, cq, prop_tiles(nx), bound, plan);
+  if ((rc = check_launch(h, "reach"))) return rc;
+  // y: ssq -> tmp; z: tmp -> ssq (+ sdf)
+  rc = launch_pass_planned<false, false>(h, ssq, tmp, nullptr, hf, nx, nz, ny,
+                                         nx, layer, cy, cz, bound, plan, s);
+  if (rc) return rc;
+  return sdf ? launch_pass_planned<true, true>(h, tmp, ssq, sdf, hf, nx, ny,
+                                               nz, layer, nx, cy, cz, bound,
+                                               plan, s)
+             : launch_pass_planned<true, false>(h, tmp, ssq, nullptr, hf, nx,
+                                                ny, nz, layer, nx, cy, cz,
+                                                bound, plan, s);
+}
+
 // --------------------------------------------------------- static build
 
 }  // namespace pcsdf
@@ -1041,7 +1204,15 @@ extern "C" int pcsdf_build_static_sdf(pcsdf_handle *hp, const pcsdf_grid *g,
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const int nx = g->nx, ny = g->ny, nz = g->nz;
   const int64_t V = (int64_t)nx * ny * nz;
-  if ((rc = ensure_buffer(h, h->tmp_buf, (size_t)V * 4, s))) return rc;
+  const int vpl = voxels_per_lane(occ_dev, ssq_dev, nx);
+  const bool planned = plan_pays(h, vpl, nx, ny, nz);
+  const size_t scratch =
+      planned ? plan_offset(V) + plan_bytes(nx, ny, nz) : (size_t)V * 4;
+  if ((rc = ensure_buffer(h, h->tmp_buf, scratch, s))) return rc;
+  if (planned) {
+    ProfScope ps(h, PCSDF_KERNEL_STATIC, s);
+    return build_planned(h, g, vpl, occ_dev, ssq_dev, sdf_dev, s);
+  }
   int32_t *tmp = reinterpret_cast<int32_t *>(h->tmp_buf.ptr);
   const float hf = (float)g->voxel_m;
   // x: occ -> ssq (as scratch); y: ssq -> tmp; z: tmp -> ssq (+ sdf)
