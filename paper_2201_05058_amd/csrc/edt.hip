@@ -1084,8 +1084,8 @@ namespace pcsdf {
 // 528 -> 288 us; 512 x 512 x 256, 200 boxes of 10-80 voxels: 1227 -> 564 us);
 // one in which it is not pays about 20 us for k_reach and the launches that
 // return at once, and gets back what the 16-bit distances save the x and y
-// passes: 514 -> 527 us at 41 M voxels, 604 -> 609 at 51 M, 1018 -> 998 at 67 M.
-// The line is where that is even.
+// passes: 514 -> 527 us at 41 M voxels, 604 -> 609 at 51 M, 1018 -> 998 at
+// 67 M.  The line is where that is even.
 constexpr int64_t kPlanVoxels = 7LL << 23;
 
 // Blocks along an axis of n voxels; 128-column tiles of nx.

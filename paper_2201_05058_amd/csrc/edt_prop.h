@@ -110,7 +110,8 @@ __global__ __launch_bounds__(64 * kXLayers) void k_pass_x_coarse(
       if (i0 < nx) {
         uint2 *p = reinterpret_cast<uint2 *>(dst + i0);
 #pragma unroll
-        for (int c = 0; c < VPL / 4; ++c) p[c] = make_uint2(v[2 * c], v[2 * c + 1]);
+        for (int c = 0; c < VPL / 4; ++c)
+          p[c] = make_uint2(v[2 * c], v[2 * c + 1]);
       }
       dst += nx;
     }
@@ -289,9 +290,10 @@ __device__ __forceinline__ uint32_t prop_step(uint32_t (&u)[N], uint32_t c) {
 inline int prop_lds(int waves) { return (waves + 1) * 2 * 2 * kPropHalo * 256; }
 
 // in_: columns of m rows at `stride`, element i of outer index o's row q at
-// o * outer_stride + q * stride + i, i < nfast (nfast, and so every row, even).  kFirst: the x
-// pass's signed 16-bit distances, else signed squares; the result, out_, is
-// 16-bit squares again or, with kLast, 32-bit ones and (kSdf) sdf.   Grid: (tiles of 128 columns) x nouter; block: ceil(m / 32) waves.
+// o * outer_stride + q * stride + i, i < nfast (even, as every row's length).
+// kFirst: the x pass's signed 16-bit distances, else signed squares; the
+// result, out_, is 16-bit squares again or, with kLast, 32-bit ones and (kSdf)
+// sdf.  Grid: (tiles of 128 columns) x nouter; block: ceil(m / 32) waves.
 template <bool kFirst, bool kLast, bool kSdf>
 __global__ __launch_bounds__(64 * kPropWaves) void k_pass_col_prop(
     const void *__restrict__ in_, void *__restrict__ out_,
@@ -345,7 +347,8 @@ __global__ __launch_bounds__(64 * kPropWaves) void k_pass_col_prop(
   {
     // Rows q0 - H - 1 .. q0 + R + H, one more on either side than u holds:
     // after the first iteration all of u is exact.
-    const int16_t *row = static_cast<const int16_t *>(in_) + base + max(q0 - H - 1, 0) * stride;  // uniform
+    const int16_t *row = static_cast<const int16_t *>(in_) + base +
+                         max(q0 - H - 1, 0) * stride;  // uniform
     uint32_t above = 0, type_above = 0;  // of the row above: value + 1, type
     // kPropBatch rows' loads are in flight while as many are taken in
     uint32_t x[2][kPropBatch];

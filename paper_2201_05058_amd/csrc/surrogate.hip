@@ -28,16 +28,24 @@
 // One call, all on the caller's stream and without host round trips:
 //   1. prep:    per query the environment value, the humans that can still
 //               matter (bounds from the residual's clamp prune the rest
-//               exactly), their count and a prefix sum over the workgroup;
+//               exactly), a bit each, and a prefix sum of their number over
+//               the workgroup;
 //   2. scan:    the workgroups' totals (one workgroup);
 //   3. rows:    the 16 features of every (query, relevant human) row;
 //   4. network: value and input gradient of every row (mlp.hip), the row
 //               count read on the device;
-//   5. decide:  the min, the rules above, answers written out; fallback
-//               queries flagged and their slices marked as needed;
+//   5. decide:  the min, the winner's gradient, the rules above, answers
+//               written out; fallback queries flagged and their slices
+//               marked as needed;
 //   6. planes:  the humans' planar fields of the marked slices only;
 //   7. exact:   the flagged queries answered exactly from the planes and
 //               the static field (direct.hip), without building a field.
+// Prep is bound by the environment samples (four lines of the field per query
+// at any place: 78 us for 10^6 queries in 256 x 256 x 128, 6.5 TB/s of lines);
+// rows and decide by fp64 roots, divisions and trigonometry, so they take the
+// humans' bits from prep, the cell's features once per query and a gradient
+// only for the winner: 45 -> 23 and 50 -> 26 us there with 3 humans (each
+// found the relevant humans again, two roots a human and pass).
 #include <cmath>
 #include <cstring>
 
@@ -49,6 +57,42 @@ namespace pcsdf {
 constexpr int kSurIn = PCSDF_SURROGATE_IN;  // features per row
 constexpr double kResLo = -0.5, kResHi = 1.5;  // residual clamp (voxels)
 constexpr double kTwoPi = 6.283185307179586476925286766559;
+
+// A human's axis seen from a query's column, in voxel units (fp64).
+struct HumanAxis {
+  int64_t X, Y;  // the fixed-point centre
+  double ux, uy;
+  bool present;  // its disk may reach a voxel centre of the grid
+  __device__ __forceinline__ double rho2() const { return ux * ux + uy * uy; }
+};
+
+__device__ __forceinline__ double human_radius(const Centres &C, int s) {
+  return (double)radius_of(C, s) / 65536.0;
+}
+
+__device__ __forceinline__ HumanAxis human_axis(const Centres &C, int K, int s,
+                                                int k, double Rv, double gx,
+                                                double gy, int nx, int ny) {
+  HumanAxis H;
+  H.X = centre_word(C, 2 * ((int64_t)s * K + k));
+  H.Y = centre_word(C, 2 * ((int64_t)s * K + k) + 1);
+  const double cx = (double)H.X / 65536.0 - 0.5;
+  const double cy = (double)H.Y / 65536.0 - 0.5;
+  H.present = !(cx + Rv < 0.0 || cx - Rv > (double)(nx - 1) ||
+                cy + Rv < 0.0 || cy - Rv > (double)(ny - 1));
+  H.ux = gx - cx;
+  H.uy = gy - cy;
+  return H;
+}
+
+// Distance to the cylinder, of an axis at squared distance rho2 and a query
+// w layers above its top: non-decreasing in rho2, rounding included.
+__device__ __forceinline__ double human_distance(double rho2, double Rv,
+                                                 double w) {
+  const double a = sqrt(rho2) - Rv;
+  const double ap = a > 0.0 ? a : 0.0, wp = w > 0.0 ? w : 0.0;
+  return sqrt(ap * ap + wp * wp);
+}
 
 // Geometry of one human seen from one query, in voxel units (fp64).
 struct HumanGeo {
@@ -62,24 +106,22 @@ __device__ __forceinline__ HumanGeo human_geo(const Centres &C, int K, int s,
                                               double gz, int Kt, int nx,
                                               int ny) {
   HumanGeo G;
-  const int64_t X = centre_word(C, 2 * ((int64_t)s * K + k));
-  const int64_t Y = centre_word(C, 2 * ((int64_t)s * K + k) + 1);
-  const double Rv = (double)radius_of(C, s) / 65536.0;
-  const double cx = (double)X / 65536.0 - 0.5;
-  const double cy = (double)Y / 65536.0 - 0.5;
-  G.present = !(cx + Rv < 0.0 || cx - Rv > (double)(nx - 1) ||
-                cy + Rv < 0.0 || cy - Rv > (double)(ny - 1));
+  const double Rv = human_radius(C, s);
+  const HumanAxis H = human_axis(C, K, s, k, Rv, gx, gy, nx, ny);
+  const double cx = (double)H.X / 65536.0 - 0.5;
+  const double cy = (double)H.Y / 65536.0 - 0.5;
+  G.present = H.present;
   G.clipped = G.present && (cx - Rv <= -1.0 || cx + Rv >= (double)nx ||
                             cy - Rv <= -1.0 || cy + Rv >= (double)ny);
-  G.ux = gx - cx;
-  G.uy = gy - cy;
-  G.rho = sqrt(G.ux * G.ux + G.uy * G.uy);
+  G.ux = H.ux;
+  G.uy = H.uy;
+  G.rho = sqrt(H.rho2());
   G.a = G.rho - Rv;
   G.w = gz - (double)Kt;
   const double ap = G.a > 0.0 ? G.a : 0.0, wp = G.w > 0.0 ? G.w : 0.0;
   G.d = sqrt(ap * ap + wp * wp);
-  G.phx = (double)((X - 32768) & 0xFFFF) / 65536.0;
-  G.phy = (double)((Y - 32768) & 0xFFFF) / 65536.0;
+  G.phx = (double)((H.X - 32768) & 0xFFFF) / 65536.0;
+  G.phy = (double)((H.Y - 32768) & 0xFFFF) / 65536.0;
   return G;
 }
 
@@ -107,8 +149,17 @@ __device__ __forceinline__ QueryPos query_pos(const float *c, double h,
 // The 16 features of one row (fp64 values rounded to fp32):
 //   [ux/rho, uy/rho, a, w, d, 1/(1+d), sin/cos 2pi phx, sin/cos 2pi phy,
 //    sin/cos 2pi f_x, sin/cos 2pi f_y, sin/cos 2pi f_z], f = g - floor(g).
+// The last six depend on the query alone.
+__device__ __forceinline__ void cell_features(const double g[3], float x[6]) {
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const double f = g[a] - floor(g[a]);
+    x[2 * a] = (float)sinpi(2.0 * f);
+    x[2 * a + 1] = (float)cospi(2.0 * f);
+  }
+}
 __device__ __forceinline__ void row_features(const HumanGeo &G,
-                                             const double g[3], float *x) {
+                                             const float cell[6], float *x) {
   const bool r0 = G.rho > 0.0;
   x[0] = (float)(r0 ? G.ux / G.rho : 0.0);
   x[1] = (float)(r0 ? G.uy / G.rho : 0.0);
@@ -121,25 +172,25 @@ __device__ __forceinline__ void row_features(const HumanGeo &G,
   x[8] = (float)sinpi(2.0 * G.phy);
   x[9] = (float)cospi(2.0 * G.phy);
 #pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    const double f = g[a] - floor(g[a]);
-    x[10 + 2 * a] = (float)sinpi(2.0 * f);
-    x[11 + 2 * a] = (float)cospi(2.0 * f);
-  }
+  for (int a = 0; a < 6; ++a) x[10 + a] = cell[a];
 }
 
-// A human's prediction y = fp32(h (d + clamp(delta))) in metres and its
-// gradient dy/dc (fp32, metres per metre): the closed-form gradient of d
+// A human's prediction y = fp32(h (d + clamp(delta))) in metres.
+__device__ __forceinline__ float human_value(double d, float delta, double h) {
+  const double dl = (double)delta;
+  const double dc = dl < kResLo ? kResLo : (dl > kResHi ? kResHi : dl);
+  return (float)(h * (d + (isnan(dl) ? dl : dc)));
+}
+
+// Its gradient dy/dc (fp32, metres per metre): the closed-form gradient of d
 // plus, when delta is not clamped, the network's feature gradient G
 // through the features' closed-form derivatives.
-__device__ __forceinline__ float human_value(const HumanGeo &Gm,
-                                             const double g[3], float delta,
-                                             const float *Gf, double h,
-                                             float grad[3]) {
+__device__ __forceinline__ void human_gradient(const HumanGeo &Gm,
+                                               const double g[3], float delta,
+                                               const float *Gf,
+                                               float grad[3]) {
   const double dl = (double)delta;
   const bool clamped = !(dl >= kResLo && dl <= kResHi);
-  const double dc = dl < kResLo ? kResLo : (dl > kResHi ? kResHi : dl);
-  const double y = h * (Gm.d + (isnan(dl) ? dl : dc));
   const bool r0 = Gm.rho > 0.0;
   const double ex = r0 ? Gm.ux / Gm.rho : 0.0, ey = r0 ? Gm.uy / Gm.rho : 0.0;
   const double ap = Gm.a > 0.0 ? Gm.a : 0.0, wp = Gm.w > 0.0 ? Gm.w : 0.0;
@@ -171,15 +222,14 @@ __device__ __forceinline__ float human_value(const HumanGeo &Gm,
   // y = h (d + delta) and dg/dc = 1/h: the metres cancel
 #pragma unroll
   for (int a = 0; a < 3; ++a) grad[a] = (float)t[a];
-  return (float)y;
 }
 
 // Lower and upper bounds of a human's prediction (the residual's clamp).
-__device__ __forceinline__ float human_lo(const HumanGeo &G, double h) {
-  return (float)(h * (G.d + kResLo));
+__device__ __forceinline__ float human_lo(double d, double h) {
+  return (float)(h * (d + kResLo));
 }
-__device__ __forceinline__ float human_hi(const HumanGeo &G, double h) {
-  return (float)(h * (G.d + kResHi));
+__device__ __forceinline__ float human_hi(double d, double h) {
+  return (float)(h * (d + kResHi));
 }
 
 struct SurArgs {
@@ -193,7 +243,7 @@ struct SurArgs {
   // per query
   float *env;      // [n][4]: e, de/dc
   int8_t *state;   // 0 pending, 1 fallback, 2 answered (slice < 0)
-  int32_t *count;  // relevant humans
+  int32_t *count;  // relevant humans: a bit each, their number with K > 32
   int32_t *loc;    // exclusive prefix within the workgroup
   int32_t *bsum;   // per workgroup: its total, then its exclusive offset
   int32_t *total;  // [1] rows
@@ -209,17 +259,80 @@ __device__ __forceinline__ int clamp_slice(int s, int n) {
   return s < 0 ? 0 : (s > n - 1 ? n - 1 : s);
 }
 
-// Is human k relevant to a pending query: present and not provably above
-// the best upper bound m_hi by more than the band?
-__device__ __forceinline__ bool relevant(const HumanGeo &G, float m_hi,
-                                         double h, double band) {
-  return G.present && !((double)human_lo(G, h) > (double)m_hi + band);
+// The humans that matter to a pending query: present and not provably above
+// the best upper bound m_hi by more than the band.  The upper bound is the
+// nearest human's (bounds do not decrease with the axis' squared distance),
+// one pair of roots instead of one per human; and a human whose squared
+// distance alone, with a millionth and a millionth of a voxel to spare, puts
+// it above m_hi + band needs none either.
+struct Relevance {
+  double limit2;  // squared axis distance above which none is relevant
+  double top;     // m_hi + band
+  float m_hi;
+};
+
+__device__ __forceinline__ Relevance relevance(const SurArgs &A, int sc,
+                                               double Rv, const double g[3],
+                                               float env) {
+  const double w = g[2] - (double)A.Kt;
+  double near2 = __builtin_inf();
+  for (int k = 0; k < A.K; ++k) {
+    const HumanAxis H = human_axis(A.C, A.K, sc, k, Rv, g[0], g[1], A.nx,
+                                   A.ny);
+    const double r2 = H.rho2();
+    if (H.present && r2 < near2) near2 = r2;
+  }
+  Relevance r;
+  r.m_hi = env;
+  if (near2 < __builtin_inf())
+    r.m_hi = fminf(r.m_hi, human_hi(human_distance(near2, Rv, w), A.h));
+  r.top = (double)r.m_hi + A.band;
+  const double t =
+      (r.top + 1e-6 * fabs(r.top)) / A.h - kResLo + 1e-6 + Rv;
+  r.limit2 = t > 0.0 ? t * t * (1.0 + 1e-9) : -1.0;
+  return r;
 }
 
+__device__ __forceinline__ bool relevant(const SurArgs &A, const Relevance &r,
+                                         int sc, int k, double Rv,
+                                         const double g[3]) {
+  const HumanAxis H = human_axis(A.C, A.K, sc, k, Rv, g[0], g[1], A.nx, A.ny);
+  const double r2 = H.rho2();
+  if (!H.present || r2 > r.limit2) return false;
+  const double d = human_distance(r2, Rv, g[2] - (double)A.Kt);
+  return !((double)human_lo(d, A.h) > r.top);
+}
+
+// The relevant humans of a query in order, f(k) for each: with kBits those of
+// its count word, else found again.
+template <bool kBits, class F>
+__device__ __forceinline__ void each_relevant(const SurArgs &A, int q, int sc,
+                                              const double g[3], float env,
+                                              F f) {
+  if (kBits) {
+    for (uint32_t m = (uint32_t)A.count[q]; m; m &= m - 1)
+      f(__builtin_ctz(m));
+  } else {
+    const double Rv = human_radius(A.C, sc);
+    const Relevance r = relevance(A, sc, Rv, g, env);
+    for (int k = 0; k < A.K; ++k)
+      if (relevant(A, r, sc, k, Rv, g)) f(k);
+  }
+}
+
+template <bool kBits>
+__device__ __forceinline__ int relevant_count(const SurArgs &A, int q) {
+  return kBits ? __builtin_popcount((uint32_t)A.count[q]) : A.count[q];
+}
+
+template <bool kBits>
 __global__ __launch_bounds__(256) void k_sur_prep(SurArgs A) {
   __shared__ int32_t wsum[4];
   const int q = blockIdx.x * 256 + threadIdx.x;
+  // (decide marks them)
+  for (int t = q; t < A.n_slices; t += (int)gridDim.x * 256) A.need[t] = 0;
   int cnt = 0;
+  uint32_t bits = 0;
   if (q < A.n) {
     const int s = A.slice[q];
     const float c3[3] = {A.centre[3 * q], A.centre[3 * q + 1],
@@ -249,27 +362,23 @@ __global__ __launch_bounds__(256) void k_sur_prep(SurArgs A) {
         A.env[4 * q + 2] = (float)(T.g[1] / A.h);
         A.env[4 * q + 3] = (float)(T.g[2] / A.h);
         const int sc = clamp_slice(s, A.n_slices);
-        float m_hi = e;
-        for (int k = 0; k < A.K; ++k) {
-          const HumanGeo G = human_geo(A.C, A.K, sc, k, P.g[0], P.g[1],
-                                       P.g[2], A.Kt, A.nx, A.ny);
-          if (G.present) m_hi = fminf(m_hi, human_hi(G, A.h));
-        }
+        const double Rv = human_radius(A.C, sc);
+        const Relevance r = relevance(A, sc, Rv, P.g, e);
         // the answer is at most m_hi: below the margin it falls back
         // whatever the network says
-        if (!(m_hi - rq >= A.margin)) {
+        if (!(r.m_hi - rq >= A.margin)) {
           st = 1;
         } else {
-          for (int k = 0; k < A.K; ++k) {
-            const HumanGeo G = human_geo(A.C, A.K, sc, k, P.g[0], P.g[1],
-                                         P.g[2], A.Kt, A.nx, A.ny);
-            cnt += relevant(G, m_hi, A.h, A.band) ? 1 : 0;
-          }
+          for (int k = 0; k < A.K; ++k)
+            if (relevant(A, r, sc, k, Rv, P.g)) {
+              ++cnt;
+              bits |= 1u << (k & 31);
+            }
         }
       }
     }
     A.state[q] = st;
-    A.count[q] = cnt;
+    A.count[q] = kBits ? (int32_t)bits : cnt;
   }
   // exclusive prefix of cnt over the workgroup
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -321,36 +430,32 @@ __device__ __forceinline__ int64_t row_offset(const SurArgs &A, int q) {
   return (int64_t)A.bsum[q >> 8] + A.loc[q];
 }
 
+template <bool kBits>
 __global__ __launch_bounds__(256) void k_sur_rows(SurArgs A) {
   const int q = blockIdx.x * 256 + threadIdx.x;
   if (q >= A.n || A.state[q] != 0 || A.count[q] == 0) return;
   const int64_t off = row_offset(A, q);
-  if (off + A.count[q] > A.cap) return;  // the query falls back
+  if (off + relevant_count<kBits>(A, q) > A.cap) return;  // falls back
   const float c3[3] = {A.centre[3 * q], A.centre[3 * q + 1],
                        A.centre[3 * q + 2]};
   const QueryPos P = query_pos(c3, A.h, A.ox, A.oy, A.oz, A.nx, A.ny, A.nz);
   const int sc = clamp_slice(A.slice[q], A.n_slices);
-  const float rq = A.radius[q];
-  (void)rq;
-  float m_hi = A.env[4 * q];
-  for (int k = 0; k < A.K; ++k) {
-    const HumanGeo G = human_geo(A.C, A.K, sc, k, P.g[0], P.g[1], P.g[2],
-                                 A.Kt, A.nx, A.ny);
-    if (G.present) m_hi = fminf(m_hi, human_hi(G, A.h));
-  }
+  float cell[6];
+  cell_features(P.g, cell);
   int64_t r = off;
-  for (int k = 0; k < A.K; ++k) {
+  each_relevant<kBits>(A, q, sc, P.g, kBits ? 0.0f : A.env[4 * q],
+                       [&](int k) {
     const HumanGeo G = human_geo(A.C, A.K, sc, k, P.g[0], P.g[1], P.g[2],
                                  A.Kt, A.nx, A.ny);
-    if (!relevant(G, m_hi, A.h, A.band)) continue;
-    row_features(G, P.g, A.x + r * kSurIn);
+    row_features(G, cell, A.x + r * kSurIn);
     ++r;
-  }
+  });
 }
 
 // Slices a workgroup marks in LDS before marking them in global memory.
 constexpr int kNeedBits = 1024;
 
+template <bool kBits>
 __global__ __launch_bounds__(256) void k_sur_decide(SurArgs A) {
   __shared__ uint32_t bits[kNeedBits / 32];
   for (int t = threadIdx.x; t < kNeedBits / 32; t += 256) bits[t] = 0u;
@@ -366,39 +471,32 @@ __global__ __launch_bounds__(256) void k_sur_decide(SurArgs A) {
       const QueryPos P = query_pos(c3, A.h, A.ox, A.oy, A.oz, A.nx, A.ny,
                                    A.nz);
       const float rq = A.radius[q];
-      const int cnt = A.count[q];
+      const int cnt = relevant_count<kBits>(A, q);
       const int64_t off = row_offset(A, q);
       fb = cnt > 0 && off + cnt > A.cap;
       float y = A.env[4 * q];
       float g[3] = {A.env[4 * q + 1], A.env[4 * q + 2], A.env[4 * q + 3]};
       float m2 = __builtin_inff(), cmin = __builtin_inff();
       if (!fb && cnt > 0) {
-        float m_hi = y;
-        for (int k = 0; k < A.K; ++k) {
+        int64_t r = off, best = -1;
+        HumanGeo W;  // the winner's
+        each_relevant<kBits>(A, q, sc, P.g, y, [&](int k) {
           const HumanGeo G = human_geo(A.C, A.K, sc, k, P.g[0], P.g[1],
                                        P.g[2], A.Kt, A.nx, A.ny);
-          if (G.present) m_hi = fminf(m_hi, human_hi(G, A.h));
-        }
-        int64_t r = off;
-        for (int k = 0; k < A.K; ++k) {
-          const HumanGeo G = human_geo(A.C, A.K, sc, k, P.g[0], P.g[1],
-                                       P.g[2], A.Kt, A.nx, A.ny);
-          if (!relevant(G, m_hi, A.h, A.band)) continue;
-          float gk[3];
-          const float yk = human_value(G, P.g, A.y[r], A.gx + r * kSurIn,
-                                       A.h, gk);
-          ++r;
+          const float yk = human_value(G.d, A.y[r], A.h);
           if (G.clipped) cmin = fminf(cmin, yk);
           if (yk < y) {
             m2 = y;
             y = yk;
-            g[0] = gk[0];
-            g[1] = gk[1];
-            g[2] = gk[2];
+            best = r;
+            W = G;
           } else if (yk < m2) {
             m2 = yk;
           }
-        }
+          ++r;
+        });
+        if (best >= 0)
+          human_gradient(W, P.g, A.y[best], A.gx + best * kSurIn, g);
       }
       const float ds = y - rq;
       const bool ok = !fb && isfinite(ds) && ds >= A.margin &&
@@ -464,7 +562,9 @@ __global__ __launch_bounds__(256) void k_sur_features(
   k = k < 0 ? 0 : (k > K - 1 ? K - 1 : k);
   const HumanGeo G = human_geo(C, K, sc, k, P.g[0], P.g[1], P.g[2], Kt, nx,
                                ny);
-  row_features(G, P.g, x + (int64_t)q * kSurIn);
+  float cell[6];
+  cell_features(P.g, cell);
+  row_features(G, cell, x + (int64_t)q * kSurIn);
   if (base) base[q] = (float)G.d;
   if (target && label) target[q] = (float)((double)label[q] / h - G.d);
 }
@@ -631,14 +731,15 @@ extern "C" int pcsdf_query_spheres_surrogate(
   A.cost = cost_dev;
   A.status = status_dev;
   A.used = used_fallback_dev ? used_fallback_dev : used_ws;
+  const bool bits = hs.K <= 32;
   {
     ProfScope ps(h, PCSDF_KERNEL_SURROGATE_DECIDE, s);
-    hipLaunchKernelGGL(k_clear, dim3(nblocks(n_slices)), dim3(256), 0, s,
-                       A.need, n_slices);
-    hipLaunchKernelGGL(k_sur_prep, dim3(nb), dim3(256), 0, s, A);
+    hipLaunchKernelGGL(bits ? k_sur_prep<true> : k_sur_prep<false>, dim3(nb),
+                       dim3(256), 0, s, A);
     hipLaunchKernelGGL(k_sur_scan, dim3(1), dim3(1024), 0, s, A.bsum, nb,
                        A.total);
-    hipLaunchKernelGGL(k_sur_rows, dim3(nb), dim3(256), 0, s, A);
+    hipLaunchKernelGGL(bits ? k_sur_rows<true> : k_sur_rows<false>, dim3(nb),
+                       dim3(256), 0, s, A);
     if ((rc = check_launch(h, "surrogate rows"))) return rc;
   }
   if (cap > 0) {
@@ -647,7 +748,8 @@ extern "C" int pcsdf_query_spheres_surrogate(
   }
   {
     ProfScope ps(h, PCSDF_KERNEL_SURROGATE_DECIDE, s);
-    hipLaunchKernelGGL(k_sur_decide, dim3(nb), dim3(256), 0, s, A);
+    hipLaunchKernelGGL(bits ? k_sur_decide<true> : k_sur_decide<false>,
+                       dim3(nb), dim3(256), 0, s, A);
     if ((rc = check_launch(h, "surrogate decide"))) return rc;
   }
   if (rows_dev)
