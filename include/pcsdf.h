@@ -370,12 +370,14 @@ int pcsdf_predicted_composite_sdf_batch(pcsdf_handle *h, int32_t n_scenes,
                                         const pcsdf_scene *scenes,
                                         void *stream);
 
-/* The same batch captured once in a hipGraph (parameter upload from pinned
- * memory owned by the graph, then the batch's two launches) and
- * replayed with one hipGraphLaunch.  The graph owns its workspace; the
- * scenes' device buffers must outlive it.  set_positions replaces one
- * scene's predicted positions for later launches (waiting for a launch
- * still reading them).  Errors of graph calls are reported through the
+/* The same batch captured in a hipGraph (parameter upload from pinned
+ * memory owned by the graph, then the batch's two launches; captured for
+ * two such copies of the parameters) and replayed with one hipGraphLaunch.
+ * The graph owns its workspace; the scenes' device buffers must outlive
+ * it.  Launches run in order, on whatever streams.  set_positions replaces
+ * one scene's predicted positions for later launches; it goes into the copy
+ * that the last launch does not read, and so waits at most for the launch
+ * before that.  Errors of graph calls are reported through the
  * creating handle. */
 typedef struct pcsdf_batch_graph pcsdf_batch_graph;
 int pcsdf_batch_graph_create(pcsdf_handle *h, int32_t n_scenes,

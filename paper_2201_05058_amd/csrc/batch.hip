@@ -117,16 +117,26 @@ static int run_batch(Handle *h, int n_scenes, const pcsdf_scene *scenes,
 
 using namespace pcsdf;
 
+// The batch captured twice, each with an upload from its own pinned copy of
+// the parameters: new positions go into the copy that the last launch does
+// not read, so that they are set, and the next launch is queued, while that
+// one runs (8 rooms, 1 ms of kernels: 77 us between launches otherwise).  The
+// device's parameters and scratch are one; launches are ordered.
 struct pcsdf_batch_graph {
+  struct Copy {
+    void *pinned = nullptr;
+    hipGraph_t graph = nullptr;
+    hipGraphExec_t exec = nullptr;
+    hipEvent_t done = nullptr;
+    bool pending = false;  // launched, and not seen to have ended
+  };
   Handle *h = nullptr;
   BatchPlan plan;
   std::vector<pcsdf_scene> scenes;
   DevBuf params, scratch;
-  void *pinned = nullptr;
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec = nullptr;
-  hipEvent_t done = nullptr;
-  bool pending = false;
+  Copy copy[2];
+  int cur = 0;           // the copy of the last launch
+  bool changed = false;  // the other one holds positions set since
 };
 
 extern "C" int pcsdf_predicted_composite_sdf_batch(pcsdf_handle *hp,
@@ -146,17 +156,20 @@ static int graph_fail(pcsdf_batch_graph *g, int code, const std::string &m) {
 
 extern "C" void pcsdf_batch_graph_destroy(pcsdf_batch_graph *g) {
   if (!g) return;
-  if (g->pending && g->done) (void)hipEventSynchronize(g->done);
-  if (g->exec) (void)hipGraphExecDestroy(g->exec);
-  if (g->graph) (void)hipGraphDestroy(g->graph);
-  if (g->done) (void)hipEventDestroy(g->done);
+  for (auto &c : g->copy) {
+    if (c.pending && c.done) (void)hipEventSynchronize(c.done);
+    if (c.exec) (void)hipGraphExecDestroy(c.exec);
+    if (c.graph) (void)hipGraphDestroy(c.graph);
+    if (c.done) (void)hipEventDestroy(c.done);
+  }
   DevBuf *bufs[] = {&g->params, &g->scratch};
   bool any = false;
   for (DevBuf *b : bufs) any = any || b->ptr;
   if (any) (void)hipDeviceSynchronize();
   for (DevBuf *b : bufs)
     if (b->ptr) (void)hipFree(b->ptr);
-  if (g->pinned) (void)hipHostFree(g->pinned);
+  for (auto &c : g->copy)
+    if (c.pinned) (void)hipHostFree(c.pinned);
   delete g;
 }
 
@@ -193,32 +206,42 @@ extern "C" int pcsdf_batch_graph_create(pcsdf_handle *hp, int32_t n_scenes,
   char *pbase = reinterpret_cast<char *>(g->params.ptr);
   bind_plan(&g->plan, scenes, pbase, reinterpret_cast<char *>(g->scratch.ptr),
             &host);
-  if (hipHostMalloc(&g->pinned, host.size(), hipHostMallocDefault) !=
-      hipSuccess) {
-    g->pinned = nullptr;
-    pcsdf_batch_graph_destroy(g);
-    return fail(h, PCSDF_ERR_OOM, "pinned staging allocation failed");
-  }
-  std::memcpy(g->pinned, host.data(), host.size());
-  if (hipEventCreateWithFlags(&g->done, hipEventDisableTiming) != hipSuccess ||
-      hipStreamCreateWithFlags(&cap, hipStreamNonBlocking) != hipSuccess) {
+  if (hipStreamCreateWithFlags(&cap, hipStreamNonBlocking) != hipSuccess) {
     pcsdf_batch_graph_destroy(g);
     return fail(h, PCSDF_ERR_HIP, "graph stream/event creation failed");
   }
-  bool ok = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal) ==
-            hipSuccess;
-  if (ok) {
-    ok = hipMemcpyAsync(pbase, g->pinned, host.size(), hipMemcpyHostToDevice,
-                        cap) == hipSuccess;
-    if (ok) ok = enqueue_batch(h, g->plan, pbase, cap) == PCSDF_OK;
-    hipGraph_t graph = nullptr;
-    const bool ended = hipStreamEndCapture(cap, &graph) == hipSuccess;
-    ok = ok && ended && graph;
-    g->graph = graph;
-  }
-  if (ok)
-    ok = hipGraphInstantiate(&g->exec, g->graph, nullptr, nullptr, 0) ==
+  bool ok = true;
+  for (auto &c : g->copy) {
+    if (hipHostMalloc(&c.pinned, host.size(), hipHostMallocDefault) !=
+        hipSuccess) {
+      c.pinned = nullptr;
+      (void)hipStreamDestroy(cap);
+      pcsdf_batch_graph_destroy(g);
+      return fail(h, PCSDF_ERR_OOM, "pinned staging allocation failed");
+    }
+    std::memcpy(c.pinned, host.data(), host.size());
+    if (hipEventCreateWithFlags(&c.done, hipEventDisableTiming) !=
+        hipSuccess) {
+      (void)hipStreamDestroy(cap);
+      pcsdf_batch_graph_destroy(g);
+      return fail(h, PCSDF_ERR_HIP, "graph stream/event creation failed");
+    }
+    ok = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal) ==
          hipSuccess;
+    if (ok) {
+      ok = hipMemcpyAsync(pbase, c.pinned, host.size(), hipMemcpyHostToDevice,
+                          cap) == hipSuccess;
+      if (ok) ok = enqueue_batch(h, g->plan, pbase, cap) == PCSDF_OK;
+      hipGraph_t graph = nullptr;
+      const bool ended = hipStreamEndCapture(cap, &graph) == hipSuccess;
+      ok = ok && ended && graph;
+      c.graph = graph;
+    }
+    if (ok)
+      ok = hipGraphInstantiate(&c.exec, c.graph, nullptr, nullptr, 0) ==
+           hipSuccess;
+    if (!ok) break;
+  }
   (void)hipStreamDestroy(cap);
   if (!ok) {
     (void)hipGetLastError();
@@ -250,15 +273,20 @@ extern "C" int pcsdf_batch_graph_set_positions(pcsdf_batch_graph *g,
       return graph_fail(g, PCSDF_ERR_NUMERIC,
                         "human position non-finite or out of range");
   }
-  if (g->pending) {
-    if (hipEventSynchronize(g->done) != hipSuccess)
-      return graph_fail(g, PCSDF_ERR_HIP, "waiting for the graph failed");
-    g->pending = false;
-  }
   const size_t off_xy = param_layout(g->plan).xy;
-  std::memcpy(static_cast<char *>(g->pinned) + off_xy +
-                  g->plan.xy_off[scene] * 8,
-              tmp.data(), tmp.size() * 8);
+  pcsdf_batch_graph::Copy &next = g->copy[g->cur ^ 1];
+  char *const xy = static_cast<char *>(next.pinned) + off_xy;
+  if (!g->changed) {
+    if (next.pending) {
+      if (hipEventSynchronize(next.done) != hipSuccess)
+        return graph_fail(g, PCSDF_ERR_HIP, "waiting for the graph failed");
+      next.pending = false;
+    }
+    std::memcpy(xy, static_cast<char *>(g->copy[g->cur].pinned) + off_xy,
+                g->plan.xy.size() * 8);
+    g->changed = true;
+  }
+  std::memcpy(xy + g->plan.xy_off[scene] * 8, tmp.data(), tmp.size() * 8);
   (void)h;
   return PCSDF_OK;
 }
@@ -266,13 +294,22 @@ extern "C" int pcsdf_batch_graph_set_positions(pcsdf_batch_graph *g,
 extern "C" int pcsdf_batch_graph_launch(pcsdf_batch_graph *g, void *stream) {
   if (!g) return PCSDF_ERR_INVALID_ARG;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  pcsdf_batch_graph::Copy &before = g->copy[g->cur];
+  pcsdf_batch_graph::Copy &c = g->copy[g->cur ^ (g->changed ? 1 : 0)];
+  // the copies share the device's parameters and scratch: on whatever stream
+  // the last launch is, this one comes after it
+  if (before.pending &&
+      hipStreamWaitEvent(s, before.done, 0) != hipSuccess)
+    return graph_fail(g, PCSDF_ERR_HIP, "ordering the graph failed");
   ProfScope ps(g->h, PCSDF_KERNEL_BATCH, s);
-  if (hipGraphLaunch(g->exec, s) != hipSuccess)
+  if (hipGraphLaunch(c.exec, s) != hipSuccess)
     return graph_fail(g, PCSDF_ERR_HIP, "hipGraphLaunch failed");
   ps.stop();
-  if (hipEventRecord(g->done, s) != hipSuccess)
+  if (hipEventRecord(c.done, s) != hipSuccess)
     return graph_fail(g, PCSDF_ERR_HIP, "hipEventRecord failed");
-  g->pending = true;
+  c.pending = true;
+  if (g->changed) g->cur ^= 1;
+  g->changed = false;
   return PCSDF_OK;
 }
 
