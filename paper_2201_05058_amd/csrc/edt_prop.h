@@ -1,6 +1,6 @@
 // The static EDT's column passes by propagation (included by edt.hip), for
 // volumes in which no voxel is farther than kReachMax voxels from the other
-// type's set.
+// type's set, or has none to be near to.
 //
 // g(q) = min over p of f(p) + (q - p)^2 along a column.  Moving one step
 // further from a site costs 1, 3, 5, ...: after iterations k = 1 .. K of
@@ -100,19 +100,8 @@ __global__ __launch_bounds__(64 * kXLayers) void k_pass_x_coarse(
       has_occ |= lo;
       has_free |= lf;
       uint32_t v[VPL / 2];
-#pragma unroll
-      for (int j = 0; j < VPL; j += 2) {
-        const int a = min(d[j], kNoDist), b = min(d[j + 1], kNoDist);
-        v[j / 2] = __builtin_amdgcn_perm(
-            (uint32_t)((mo >> (j + 1)) & 1u ? -b : b),
-            (uint32_t)((mo >> j) & 1u ? -a : a), 0x05040100u);
-      }
-      if (i0 < nx) {
-        uint2 *p = reinterpret_cast<uint2 *>(dst + i0);
-#pragma unroll
-        for (int c = 0; c < VPL / 4; ++c)
-          p[c] = make_uint2(v[2 * c], v[2 * c + 1]);
-      }
+      x_words<VPL>(d, mo, v);
+      if (i0 < nx) x_store<VPL>(dst + i0, v);
       dst += nx;
     }
   }
@@ -238,6 +227,7 @@ constexpr int kPropBatch = 7;   // rows loaded together
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 typedef int16_t i16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t pair16 __attribute__((aligned(2)));  // two 16-bit elements
 typedef int32_t i32x2u __attribute__((ext_vector_type(2), aligned(4)));
 typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
 
@@ -290,7 +280,7 @@ __device__ __forceinline__ uint32_t prop_step(uint32_t (&u)[N], uint32_t c) {
 inline int prop_lds(int waves) { return (waves + 1) * 2 * 2 * kPropHalo * 256; }
 
 // in_: columns of m rows at `stride`, element i of outer index o's row q at
-// o * outer_stride + q * stride + i, i < nfast (even, as every row's length).
+// o * outer_stride + q * stride + i, i < nfast (nfast >= 2).
 // kFirst: the x pass's signed 16-bit distances, else signed squares; the
 // result, out_, is 16-bit squares again or, with kLast, 32-bit ones and (kSdf)
 // sdf.  Grid: (tiles of 128 columns) x nouter; block: ceil(m / 32) waves.
@@ -303,23 +293,26 @@ __global__ __launch_bounds__(64 * kPropWaves) void k_pass_col_prop(
   constexpr int H = kPropHalo, R = kPropRows, N = R + 2 * H, B = R / 16;
   extern __shared__ uint32_t edge[];  // [2][waves + 1][2][H][64]
   __shared__ int flag[2][kPropWaves];
-  if (!plan->near) return;
+  if (plan && !plan->near) return;
   __shared__ int limits[kPropWaves];
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int waves = blockDim.x >> 6;
   const int o = blockIdx.x / tiles, tile = blockIdx.x - o * tiles;
   const int i0 = tile * kPropCols + 2 * lane;
-  // lanes past the last column (nfast is even) take the last two again
+  // lanes at or past the last column take the last two again; one with an
+  // odd last column so has it as its pair's second
   const int ip = min(i0, nfast - 2);
-  const bool active = i0 < nfast;
+  const bool pair = i0 + 1 < nfast, single = i0 + 1 == nfast;
   const int q0 = w * R;
   const int64_t base = o * outer_stride;
 
   // The iterations of this wave's rows, and the workgroup's most.  The
   // column runs along y (kFirst) or z; along the other axis it is at o.
-  int limit = 0, longest = 0;
-  {
+  // Without a plan, none is left out.
+  int limit = m, longest = m;
+  if (plan) {
+    limit = longest = 0;
     const int n = cy * cz;
     for (int c = lane; c < n; c += 64) {
       const int b = bound[tile * n + c];
@@ -357,7 +350,7 @@ __global__ __launch_bounds__(64 * kPropWaves) void k_pass_col_prop(
       for (int e = 0; e < kPropBatch; ++e) {
         const int q = q0 - H - 1 + j0 + e;
         x[(j0 / kPropBatch) & 1][e] =
-            *reinterpret_cast<const uint32_t *>(row + (uint32_t)ip);
+            *reinterpret_cast<const pair16 *>(row + (uint32_t)ip);
         // on to row q + 1, if q and it are rows (no branches: masks)
         row += stride & ~(int64_t)((q | (m - 2 - q)) >> 31);
       }
@@ -469,19 +462,27 @@ __global__ __launch_bounds__(64 * kPropWaves) void k_pass_col_prop(
         const i16x2 s = as<i16x2>(neg[r / 16] << (15 - r % 16)) >> 15;
         const i16x2 x = as<i16x2>(v) - (int16_t)kBias;
         const uint32_t sv = bits((x ^ s) - s);
-        if (active)
-          *reinterpret_cast<uint32_t *>(dst16 + (uint32_t)i0) = sv;
+        if (pair)
+          *reinterpret_cast<pair16 *>(dst16 + (uint32_t)i0) = sv;
+        else if (single)
+          dst16[(uint32_t)i0] = (int16_t)(sv >> 16);
       } else {
-        const int32_t a = (int32_t)(v & 0xFFFFu) - kBias;
-        const int32_t b = (int32_t)(v >> 16) - kBias;
+        // (kFar16 is left where there is no site at all)
+        int32_t a = (int32_t)(v & 0xFFFFu) - kBias;
+        int32_t b = (int32_t)(v >> 16) - kBias;
+        a = a == kFar16 ? kInf : a;
+        b = b == kFar16 ? kInf : b;
         const int32_t sa = (int32_t)(neg[r / 16] << (31 - r % 16)) >> 31;
         const int32_t sb = (int32_t)(neg[r / 16] << (15 - r % 16)) >> 31;
         const int32_t va = (a ^ sa) - sa, vb = (b ^ sb) - sb;
-        if (active) {
+        if (pair) {
           *reinterpret_cast<i32x2u *>(dst + (uint32_t)i0) = i32x2u{va, vb};
           if (kSdf)
             *reinterpret_cast<f32x2u *>(fdst + (uint32_t)i0) =
                 f32x2u{ssq_to_metres(va, hf), ssq_to_metres(vb, hf)};
+        } else if (single) {
+          dst[(uint32_t)i0] = vb;
+          if (kSdf) fdst[(uint32_t)i0] = ssq_to_metres(vb, hf);
         }
       }
     }
