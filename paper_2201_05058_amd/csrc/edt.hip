@@ -32,9 +32,9 @@
 //     so the envelope has no division.  Columns too long for the segmented
 //     kernel's LDS run both channels in one wave per 32 columns
 //     (k_pass_col), and passes with few columns one lane per voxel
-//     (k_pass_col_search).  Small grids, and large ones in which every
-//     voxel has one of the other type near, propagate both channels along
-//     the columns in registers instead (edt_prop.h).
+//     (k_pass_col_search).  Short columns, small grids, and large ones in
+//     which every voxel has one of the other type near propagate both
+//     channels along the columns in registers instead (edt_prop.h).
 #include "device_common.h"
 #include "internal.h"
 
@@ -895,6 +895,12 @@ __global__ __launch_bounds__(256) void k_pass_col_inside(
 // Rows per lane of the free set's channel.
 constexpr int kInsideRows = 4;
 
+}  // namespace pcsdf
+
+#include "edt_prop.h"
+
+namespace pcsdf {
+
 // Column tiles below which a pass runs one lane per voxel.
 constexpr int64_t kSearchTiles = 64;
 
@@ -957,13 +963,24 @@ static int ensure_side_stream(Handle *h) {
   return PCSDF_OK;
 }
 
-// Segments per column: the tuning's, else one per 32 voxels of the column
-// (at most 8: 16 waves of this kernel exceed the registers of a CU's
-// share and were measured slower).
+// Segments per column: the tuning's, else so many that each has 24 to 64
+// voxels (at most 8: 16 waves of this kernel exceed the registers of a CU's
+// share and were measured slower).  Four from 96 on: with two, 300 x 100 x 100
+// took 104 us instead of 83, 512 x 512 x 120 458 instead of 401; but eight
+// only from 256 on: 250 x 250 x 250 takes 247 us with four, 272 with eight.
 static int column_segments(const Handle *h, int m) {
   if (h->tuning.static_segments > 0) return h->tuning.static_segments;
-  return m >= 256 ? 8 : m >= 128 ? 4 : m >= 64 ? 2 : 1;
+  return m >= 256 ? 8 : m >= 96 ? 4 : m >= 64 ? 2 : 1;
 }
+
+// Columns of fewer rows propagate in 32 bits (k_pass_col_prop, both channels
+// in one launch): the work grows with the distances found, so at most with
+// the column's length, where k_pass_col's single wave runs the column up and
+// down.  512 x 512 x 48 with 100 boxes 240 -> 174 us, 182 x 62 x 31 75 -> 34.
+// From 64 rows on two segments win: 512 x 512 x 64 200 us, 220 propagated;
+// 400 x 80 x 80 with four boxes 81, 89.
+constexpr int kShortRows = 64;
+constexpr int kOneWaveRows = 48;  // (two waves of 32 rows: 240 -> 212 us)
 
 // Both channels of a pass by segments.  The free set's channel of the
 // occupied voxels by search, on the side stream (use_side), beside the
@@ -1044,6 +1061,26 @@ int launch_pass_col(Handle *h, const int32_t *in, int32_t *out,
                          stride, outer_stride);
     return check_launch(h, "pass_col_search");
   }
+  const int64_t nblocks64 = (int64_t)((nfast + 63) / 64) * nouter;
+  if (h->tuning.static_segments == 0 && m >= 2 && m < kShortRows &&
+      nblocks64 < 1LL << 31) {
+    const bool one = m <= kOneWaveRows;
+    const int waves = one ? 1 : (m + kPropRows - 1) / kPropRows;
+    auto go = [&](auto kernel) {
+      launch_timed(h, kernel, dim3((unsigned)nblocks64),
+                   dim3(64 * waves), (size_t)prop_lds(waves), s,
+                   (const void *)in, (void *)out, sdf_out, h_f, nfast, m,
+                   stride, outer_stride, (nfast + 63) / 64, 0, 0,
+                   (const int32_t *)nullptr, (const EdtPlan *)nullptr);
+    };
+    if (m > kPropRows && one)
+      sdf_out ? go(&k_pass_col_prop<true, kOneWaveRows, false, true, true>)
+              : go(&k_pass_col_prop<true, kOneWaveRows, false, true, false>);
+    else
+      sdf_out ? go(&k_pass_col_prop<true, kPropRows, false, true, true>)
+              : go(&k_pass_col_prop<true, kPropRows, false, true, false>);
+    return check_launch(h, "pass_col_prop");
+  }
   auto none = [] { return PCSDF_OK; };
   int S = column_segments(h, m);
   while (S > 1 && S > m) S >>= 1;  // a power of two, at most m
@@ -1104,12 +1141,6 @@ int launch_pass_col(Handle *h, const int32_t *in, int32_t *out,
   return check_launch(h, "pass_col_global_stack");
 }
 
-}  // namespace pcsdf
-
-#include "edt_prop.h"
-
-namespace pcsdf {
-
 // ---------------------------------------------- static build, large volumes
 
 // Voxels from which a build looks whether all is near (edt_prop.h).  A build
@@ -1151,7 +1182,7 @@ static int launch_prop(Handle *h, const int32_t *in, int32_t *out, float *sdf,
                        hipStream_t s) {
   const int tiles = prop_tiles(nfast);
   const int waves = (m + kPropRows - 1) / kPropRows;
-  launch_timed(h, k_pass_col_prop<!kLast, kLast, kSdf>,
+  launch_timed(h, k_pass_col_prop<false, kPropRows, !kLast, kLast, kSdf>,
                dim3((unsigned)((int64_t)tiles * nouter)), dim3(64 * waves),
                (size_t)prop_lds(waves), s, (const void *)in, (void *)out, sdf,
                hf, nfast, m, stride, outer_stride, tiles, cy, cz, bound, plan);

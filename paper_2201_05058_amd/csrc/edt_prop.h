@@ -1,6 +1,7 @@
 // The static EDT's column passes by propagation (included by edt.hip), for
 // volumes in which no voxel is farther than kReachMax voxels from the other
-// type's set, or has none to be near to.
+// type's set, or has none to be near to; and, in 32 bits (kWide), for short
+// columns whatever the distances.
 //
 // g(q) = min over p of f(p) + (q - p)^2 along a column.  Moving one step
 // further from a site costs 1, 3, 5, ...: after iterations k = 1 .. K of
@@ -218,7 +219,7 @@ __global__ __launch_bounds__(1024) void k_reach(
 
 // ------------------------------------------------------------ the passes
 
-constexpr int kPropRows = 32;   // rows per wave
+constexpr int kPropRows = 32;   // rows per wave (R; 48 where one is enough)
 constexpr int kPropWaves = 16;  // waves per workgroup, at most
 constexpr int kPropHalo = 4;    // rows from either neighbour, iterations
                                 // between exchanges
@@ -242,20 +243,43 @@ __device__ __forceinline__ uint32_t bits(T v) {
 __device__ __forceinline__ uint32_t add2(uint32_t a, uint32_t b) {
   return bits(as<u16x2>(a) + as<u16x2>(b));
 }
-// minimum of three positive fp16 patterns, in both halves
-__device__ __forceinline__ uint32_t min2(uint32_t a, uint32_t b, uint32_t c) {
+// Minimum of three: of positive fp16 patterns in both halves, or (kWide) of
+// whole words.
+template <bool kWide>
+__device__ __forceinline__ uint32_t min3(uint32_t a, uint32_t b, uint32_t c) {
+  if constexpr (kWide) return min(min(a, b), c);
   return bits(__builtin_elementwise_minimum(
       __builtin_elementwise_minimum(as<f16x2>(a), as<f16x2>(b)),
       as<f16x2>(c)));
 }
 
+// 32-bit values, one column a lane: no distance is too far for them.
+constexpr int32_t kNone32 = 1 << 30;
+
 // One iteration over rows 1 .. N-2 of u (the outermost rows only give), step
 // cost c in both halves; with kTrack, the bits that changed in the own rows.
 // A row's new value takes the register that the row before it in the sweep
 // left; sweeps up and down in turn leave every row where it was.
-template <int N, bool kUp, bool kTrack>
+template <bool kWide, int N, bool kUp, bool kTrack>
 __device__ __forceinline__ uint32_t prop_step(uint32_t (&u)[N], uint32_t c) {
   constexpr int H = kPropHalo, d = kUp ? -1 : 1;
+  if constexpr (kWide) {
+    uint32_t prev = kUp ? u[N - 1] : u[0], acc = 0;
+    asm volatile("" : "+s"(c));  // one sum per row, not of three
+#pragma unroll
+    for (int e = 1; e < N - 1; ++e) {
+      const int j = (kUp ? N - 1 : 0) + d * e;
+      const uint32_t x = u[j];
+      uint32_t v = min(x, min(prev, u[j + d]) + c);
+      // (or the compiler forms sums of two iterations, and runs out of
+      // registers)
+      asm volatile("" : "+v"(v));
+      u[j] = v;
+      if (kTrack && j >= H && j < N - H) acc |= u[j] ^ x;
+      prev = x;
+    }
+    return acc;
+  }
   constexpr int first = kUp ? N - 1 : 0;
   uint32_t before = add2(u[first], c), acc = 0;
   uint32_t here = add2(u[first + d], c), after = add2(u[first + 2 * d], c);
@@ -266,7 +290,7 @@ __device__ __forceinline__ uint32_t prop_step(uint32_t (&u)[N], uint32_t c) {
     // cannot follow one that it depends on at once)
     const uint32_t ahead = e < N - 2 ? add2(u[j + 2 * d], c) : 0u;
     const uint32_t x = u[j];
-    u[j] = min2(x, before, after);
+    u[j] = min3<false>(x, before, after);
     if (kTrack && j >= H && j < N - H) acc |= u[j] ^ x;
     before = here;
     here = after;
@@ -280,29 +304,34 @@ __device__ __forceinline__ uint32_t prop_step(uint32_t (&u)[N], uint32_t c) {
 inline int prop_lds(int waves) { return (waves + 1) * 2 * 2 * kPropHalo * 256; }
 
 // in_: columns of m rows at `stride`, element i of outer index o's row q at
-// o * outer_stride + q * stride + i, i < nfast (nfast >= 2).
-// kFirst: the x pass's signed 16-bit distances, else signed squares; the
-// result, out_, is 16-bit squares again or, with kLast, 32-bit ones and (kSdf)
-// sdf.  Grid: (tiles of 128 columns) x nouter; block: ceil(m / 32) waves.
-template <bool kFirst, bool kLast, bool kSdf>
+// o * outer_stride + q * stride + i, i < nfast (2 at least).  In pairs, in_
+// holds with kFirst the x pass's signed 16-bit distances, else signed
+// squares; the result, out_, is 16-bit squares again or, with kLast, 32-bit
+// ones and (kSdf) sdf.  kWide: squares of 32 bits in and out, whatever
+// their size, one column a lane.  Grid: (tiles of 128 columns, kWide: 64) x
+// nouter; block: ceil(m / R) waves.
+template <bool kWide, int R, bool kFirst, bool kLast, bool kSdf>
 __global__ __launch_bounds__(64 * kPropWaves) void k_pass_col_prop(
     const void *__restrict__ in_, void *__restrict__ out_,
     float *__restrict__ sdf, float hf, int nfast, int m, int64_t stride,
     int64_t outer_stride, int tiles, int cy, int cz,
     const int32_t *__restrict__ bound, const EdtPlan *__restrict__ plan) {
-  constexpr int H = kPropHalo, R = kPropRows, N = R + 2 * H, B = R / 16;
+  constexpr int H = kPropHalo, N = R + 2 * H;
+  constexpr int kSigns = kWide ? 32 : 16, B = (R + kSigns - 1) / kSigns;  // rows a word
+  constexpr int kCols = kWide ? 1 : 2;                     // per lane
+  typedef typename std::conditional<kWide, int32_t, int16_t>::type T;
   extern __shared__ uint32_t edge[];  // [2][waves + 1][2][H][64]
   __shared__ int flag[2][kPropWaves];
-  if (plan && !plan->near) return;
+  if (!kWide && plan && !plan->near) return;
   __shared__ int limits[kPropWaves];
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int waves = blockDim.x >> 6;
   const int o = blockIdx.x / tiles, tile = blockIdx.x - o * tiles;
-  const int i0 = tile * kPropCols + 2 * lane;
-  // lanes at or past the last column take the last two again; one with an
+  const int i0 = kCols * (tile * 64 + lane);
+  // lanes at or past the last column take the last (two) again; one with an
   // odd last column so has it as its pair's second
-  const int ip = min(i0, nfast - 2);
+  const int ip = min(i0, nfast - kCols);
   const bool pair = i0 + 1 < nfast, single = i0 + 1 == nfast;
   const int q0 = w * R;
   const int64_t base = o * outer_stride;
@@ -311,7 +340,7 @@ __global__ __launch_bounds__(64 * kPropWaves) void k_pass_col_prop(
   // column runs along y (kFirst) or z; along the other axis it is at o.
   // Without a plan, none is left out.
   int limit = m, longest = m;
-  if (plan) {
+  if (!kWide && plan) {
     limit = longest = 0;
     const int n = cy * cz;
     for (int c = lane; c < n; c += 64) {
@@ -335,27 +364,34 @@ __global__ __launch_bounds__(64 * kPropWaves) void k_pass_col_prop(
     longest = __builtin_amdgcn_readfirstlane(longest);
   }
 
+  constexpr uint32_t kCap =
+      kWide ? (uint32_t)kNone32 : kPairs * (kBias + kFar16);  // none
   uint32_t u[N];
   uint32_t neg[B] = {};  // the own rows' signs, a row per bit of a half
   {
     // Rows q0 - H - 1 .. q0 + R + H, one more on either side than u holds:
     // after the first iteration all of u is exact.
-    const int16_t *row = static_cast<const int16_t *>(in_) + base +
-                         max(q0 - H - 1, 0) * stride;  // uniform
+    const T *row = static_cast<const T *>(in_) + base +
+                   max(q0 - H - 1, 0) * stride;  // uniform
+    // next to a border, and anywhere
+    constexpr uint32_t kCap1 = kWide ? 1u : kPairs * (kBias + 1);
     uint32_t above = 0, type_above = 0;  // of the row above: value + 1, type
     // kPropBatch rows' loads are in flight while as many are taken in
     uint32_t x[2][kPropBatch];
     auto load = [&](int j0) {
 #pragma unroll
       for (int e = 0; e < kPropBatch; ++e) {
+        if (j0 + e >= N + 2) break;
         const int q = q0 - H - 1 + j0 + e;
-        x[(j0 / kPropBatch) & 1][e] =
-            *reinterpret_cast<const pair16 *>(row + (uint32_t)ip);
+        if constexpr (kWide)
+          x[(j0 / kPropBatch) & 1][e] = (uint32_t)row[(uint32_t)ip];
+        else
+          x[(j0 / kPropBatch) & 1][e] =
+              *reinterpret_cast<const pair16 *>(row + (uint32_t)ip);
         // on to row q + 1, if q and it are rows (no branches: masks)
         row += stride & ~(int64_t)((q | (m - 2 - q)) >> 31);
       }
     };
-    static_assert((N + 2) % kPropBatch == 0, "whole batches");
     load(0);
 #pragma unroll
     for (int j0 = 0; j0 < N + 2; j0 += kPropBatch) {
@@ -364,26 +400,36 @@ __global__ __launch_bounds__(64 * kPropWaves) void k_pass_col_prop(
 #pragma unroll
       for (int e = 0; e < kPropBatch; ++e) {
         const int j = j0 + e, q = q0 - H - 1 + j;  // u[j - 1] is row q
-        const i16x2 s = as<i16x2>(x[(j0 / kPropBatch) & 1][e]);
-        const uint32_t type = bits(s >> 15);  // all ones where occupied
-        uint32_t v = bits(__builtin_elementwise_max(s, -s));
-        // beyond the column there is none (and, rows repeated, no border)
-        v |= (uint32_t)((q | (m - 1 - q)) >> 31) & 0x7FFF7FFFu;
-        v = bits(__builtin_elementwise_min(
-            as<u16x2>(v),
-            as<u16x2>(kPairs * (uint32_t)(kFirst ? kFarDist : kFar16))));
-        if (kFirst) v = bits(as<u16x2>(v) * as<u16x2>(v));
-        v = add2(v, kPairs * kBias);
-        const uint32_t step = add2(v, kPairs);
+        if (j >= N + 2) break;
+        const uint32_t in = x[(j0 / kPropBatch) & 1][e];
+        // beyond the column there is no site (and, rows repeated, no border)
+        const uint32_t gone = (uint32_t)((q | (m - 1 - q)) >> 31);
+        uint32_t type, v, step;  // type: all ones where occupied
+        if constexpr (kWide) {
+          type = (uint32_t)((int32_t)in >> 31);
+          v = (uint32_t)max((int32_t)in, -(int32_t)in) | (gone >> 1);
+          v = min(v, (uint32_t)kNone32);
+          step = v + 1;
+        } else {
+          const i16x2 s = as<i16x2>(in);
+          type = bits(s >> 15);
+          v = bits(__builtin_elementwise_max(s, -s)) | (gone & 0x7FFF7FFFu);
+          v = bits(__builtin_elementwise_min(
+              as<u16x2>(v),
+              as<u16x2>(kPairs * (uint32_t)(kFirst ? kFarDist : kFar16))));
+          if (kFirst) v = bits(as<u16x2>(v) * as<u16x2>(v));
+          v = add2(v, kPairs * kBias);
+          step = add2(v, kPairs);
+        }
         const uint32_t differ = type ^ type_above;
-        const uint32_t cap = (differ & kPairs * (kBias + 1)) |
-                             (~differ & kPairs * (kBias + kFar16));
-        if (j >= 2) u[j - 2] = min2(u[j - 2], step, cap);
-        if (j >= 1 && j <= N) u[j - 1] = min2(v, above, cap);
+        const uint32_t cap = (differ & kCap1) | (~differ & kCap);
+        if (j >= 2) u[j - 2] = min3<kWide>(u[j - 2], step, cap);
+        if (j >= 1 && j <= N) u[j - 1] = min3<kWide>(v, above, cap);
         above = step;
         type_above = type;
         if (j > H && j <= R + H)
-          neg[(j - H - 1) / 16] |= type & (kPairs << ((j - H - 1) % 16));
+          neg[(j - H - 1) / kSigns] |=
+              type & ((kWide ? 1u : kPairs) << ((j - H - 1) % kSigns));
       }
       // computed here, not where they are first used
 #pragma unroll
@@ -406,20 +452,20 @@ __global__ __launch_bounds__(64 * kPropWaves) void k_pass_col_prop(
 #pragma unroll
   for (int e = 0; e < H; ++e) {  // no rows beyond the column
     if (w == 0)
-      above[e * 64] = above[other + e * 64] = kPairs * (kBias + kFar16);
+      above[e * 64] = above[other + e * 64] = kCap;
     if (w == waves - 1)
-      below[(H + e) * 64] = below[other + (H + e) * 64] =
-          kPairs * (kBias + kFar16);
+      below[(H + e) * 64] = below[other + (H + e) * 64] = kCap;
   }
   int p = 0, buf = 0;
   for (int k = 2;; k += H) {
     bool ch = false;
     if (run) {
-      const uint32_t c = kPairs * (uint32_t)(2 * k - 1);
-      prop_step<N, false, false>(u, c);
-      prop_step<N, true, false>(u, c + 2 * kPairs);
-      prop_step<N, false, false>(u, c + 4 * kPairs);
-      uint32_t acc = prop_step<N, true, true>(u, c + 6 * kPairs);
+      constexpr uint32_t kOne = kWide ? 1u : kPairs;
+      const uint32_t c = kOne * (uint32_t)(2 * k - 1);
+      prop_step<kWide, N, false, false>(u, c);
+      prop_step<kWide, N, true, false>(u, c + 2 * kOne);
+      prop_step<kWide, N, false, false>(u, c + 4 * kOne);
+      uint32_t acc = prop_step<kWide, N, true, true>(u, c + 6 * kOne);
       asm volatile("" : "+v"(acc));  // one word, not a flag per row
       ch = __ballot(acc != 0) != 0;
     }
@@ -458,7 +504,16 @@ __global__ __launch_bounds__(64 * kPropWaves) void k_pass_col_prop(
   for (int r = 0; r < R; ++r) {
     if (q0 + r < m) {  // uniform
       const uint32_t v = u[H + r];
-      if (!kLast) {
+      if constexpr (kWide) {
+        int32_t a = (int32_t)v;
+        a = a >= kNone32 ? kInf : a;
+        const int32_t sa = (int32_t)(neg[r / 32] << (31 - r % 32)) >> 31;
+        a = (a ^ sa) - sa;
+        if (i0 < nfast) {
+          dst[(uint32_t)i0] = a;
+          if (kSdf) fdst[(uint32_t)i0] = ssq_to_metres(a, hf);
+        }
+      } else if (!kLast) {
         const i16x2 s = as<i16x2>(neg[r / 16] << (15 - r % 16)) >> 15;
         const i16x2 x = as<i16x2>(v) - (int16_t)kBias;
         const uint32_t sv = bits((x ^ s) - s);
@@ -486,8 +541,8 @@ __global__ __launch_bounds__(64 * kPropWaves) void k_pass_col_prop(
         }
       }
     }
-    if (!kLast) dst16 += stride;
-    if (kLast) dst += stride;
+    if (!kWide && !kLast) dst16 += stride;
+    if (kWide || kLast) dst += stride;
     if (kSdf) fdst += stride;
   }
 }
