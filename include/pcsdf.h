@@ -331,8 +331,9 @@ typedef struct pcsdf_tuning {
                                          one workgroup per composite item */
   int32_t static_segments;            /* static EDT column passes: segments
                                          (one wave each) per column, 1, 2,
-                                         4 or 8; 0: one per 32 voxels of
-                                         the column, at most 8 */
+                                         4 or 8; 0: by the column's length,
+                                         or columns that propagate without
+                                         segments */
   int32_t composite_order;            /* composite, with slices per block
                                          row chosen: 0 blocks in flight
                                          write the same few slices over

@@ -101,9 +101,10 @@ def composite_outputs(n, shape_zyx, device, want_ssq=True, want_sdf=True):
     metres) as the composite calls allocate them by default: both in one
     allocation, the fp32 field starting on the first 128-byte line at least
     4 KiB past the end of the int32 one (so that both start on a line: the
-    kernel cuts its packs at the lines of one of them).  Two output streams whose starts differ by a multiple of 8 KiB (as
-    two separate large allocations do) write measurably more slowly on
-    this GPU (256x256x128 x 20 slices: 0.239 against 0.231 ms)."""
+    kernel cuts its packs at the lines of one of them).  Two output streams
+    whose starts differ by a multiple of 8 KiB (as two separate large
+    allocations do) write measurably more slowly on this GPU (256x256x128 x
+    20 slices: 0.239 against 0.231 ms)."""
     torch = _torch()
     cnt = int(n)
     for d in shape_zyx:
