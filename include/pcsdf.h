@@ -112,7 +112,7 @@ const char *pcsdf_status_string(int status);
  *   occ_dev  [V] uint8, nonzero = occupied.             (device, read)
  *   ssq_dev  [V] int32 SSQ of the occupied set.         (device, written)
  *   sdf_dev  [V] fp32 F(SSQ), may be NULL.              (device, written)
- * Uses a workspace of 4*V bytes, and up to 33 KB more from 7*2^23 voxels
+ * Uses a workspace of 4*V bytes, and up to 33 KB more from 3*2^24 voxels
  * on.  Exact: the int32 result is unique.
  * Part of the work may run on a second stream the handle owns (created at
  * the first call that needs it, destroyed with the handle), ordered after

@@ -1146,11 +1146,11 @@ int launch_pass_col(Handle *h, const int32_t *in, int32_t *out,
 // Voxels from which a build looks whether all is near (edt_prop.h).  A build
 // in which all is near gains at any size measured (256 x 512 x 256, 300 boxes:
 // 528 -> 288 us; 512 x 512 x 256, 200 boxes of 10-80 voxels: 1227 -> 564 us);
-// one in which it is not pays about 20 us for k_reach and the launches that
+// one in which it is not pays about 18 us for k_reach and the launches that
 // return at once, and gets back what the 16-bit distances save the x and y
-// passes: 514 -> 527 us at 41 M voxels, 604 -> 609 at 51 M, 1018 -> 998 at
-// 67 M.  The line is where that is even.
-constexpr int64_t kPlanVoxels = 7LL << 23;
+// passes: 376 -> 381 us at 34 M voxels, 515 -> 521 at 41 M, 602 -> 603 at
+// 51 M, 1018 -> 995 at 67 M.  The line is where that is even.
+constexpr int64_t kPlanVoxels = 3LL << 24;
 
 // Blocks along an axis of n voxels; 128-column tiles of nx.
 static int coarse(int n) { return (n + kCoarse - 1) / kCoarse; }

@@ -141,12 +141,18 @@ __global__ __launch_bounds__(1024) void k_reach(
   const bool in = r < n;
   uint64_t occ = 0, fre = 0;
   constexpr int kPer = kCoarse / kXLayers;
+  {
+    uint64_t o[kPer], f[kPer];
 #pragma unroll
-  for (int e = 0; e < kPer; ++e) {
-    const int q = min(z * kPer + e, cq - 1);
-    if (in) {
-      occ |= occ_bits[q * cy + y];
-      fre |= free_bits[q * cy + y];
+    for (int e = 0; e < kPer; ++e) {
+      const int q = in ? min(z * kPer + e, cq - 1) * cy + y : 0;
+      o[e] = occ_bits[q];
+      f[e] = free_bits[q];
+    }
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+      occ |= in ? o[e] : 0ull;
+      fre |= in ? f[e] : 0ull;
     }
   }
   const uint64_t need_occ = fre, need_free = occ;
@@ -164,11 +170,12 @@ __global__ __launch_bounds__(1024) void k_reach(
     grown[turn][0][r] = occ;
     grown[turn][1][r] = fre;
   };
-  auto take = [&](int c, bool ok, int d) -> uint64_t {
-    return ok ? grown[turn][c][r + d] : 0ull;
-  };
-  const bool up = in && y > 0, down = in && y + 1 < cy;
-  const bool front = in && z > 0, back = in && z + 1 < cz;
+  // a neighbouring row, or (no branches) the own one where there is none
+  auto take = [&](int c, int row) { return grown[turn][c][row]; };
+  const int up = in && y > 0 ? r - 1 : r;
+  const int down = in && y + 1 < cy ? r + 1 : r;
+  const int front = in && z > 0 ? r - cy : r;
+  const int back = in && z + 1 < cz ? r + cy : r;
   const int per = kPropCols / fx;  // blocks of a tile
   bool found = false;
   uint64_t open = need_occ | need_free;  // blocks whose bound is not known
@@ -200,18 +207,16 @@ __global__ __launch_bounds__(1024) void k_reach(
     if (threadIdx.x == 0) blank[(step + 2) % 3] = 0;
     if (cube) {
       ++a;
-      occ |= take(0, up, -1) | take(0, down, 1);
-      fre |= take(1, up, -1) | take(1, down, 1);
+      occ |= take(0, up) | take(0, down);
+      fre |= take(1, up) | take(1, down);
       put();
       __syncthreads();
-      occ |= take(0, front, -cy) | take(0, back, cy);
-      fre |= take(1, front, -cy) | take(1, back, cy);
+      occ |= take(0, front) | take(0, back);
+      fre |= take(1, front) | take(1, back);
     } else {
       ++b;
-      occ = wo | take(0, up, -1) | take(0, down, 1) | take(0, front, -cy) |
-            take(0, back, cy);
-      fre = wf | take(1, up, -1) | take(1, down, 1) | take(1, front, -cy) |
-            take(1, back, cy);
+      occ = wo | take(0, up) | take(0, down) | take(0, front) | take(0, back);
+      fre = wf | take(1, up) | take(1, down) | take(1, front) | take(1, back);
     }
   }
   if (threadIdx.x == 0) plan->near = found;
