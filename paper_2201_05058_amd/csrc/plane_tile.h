@@ -1,7 +1,8 @@
 // Planar signed field of a slice's disks in one step, tile by tile: the
 // workgroup builds the chords of the slice's disks in LDS (only the rows a
 // disk covers), then each wave evaluates 64 columns x 8 rows of pixels, a
-// lane holding the eight rows of its column.  Shared by the per-call kernel
+// lane holding the eight rows of its column (G = 8 below; small calls take
+// fewer, planes.hip).  Shared by the per-call kernel
 // (planes.hip) and the batch's planar items (batch_device.h).
 //
 // A chord serves a whole wave: the row's index is uniform, the distance of
@@ -44,16 +45,18 @@ constexpr int32_t kTileFar = 1 << 24;
 constexpr int32_t kTileUnset = 1 << 30;
 
 // Rows on either side of a wave's own whose coverage it holds as bits, one
-// row per lane.
-constexpr int kTileReach = (64 - kTileRows) / 2;
+// row per lane, with G rows of a column per lane.
+constexpr int tile_reach(int G) { return (64 - G) / 2; }
+constexpr int kTileReach = tile_reach(kTileRows);
 
 // Tiles of a plane, numbered row-major.
 __host__ __device__ inline int plane_tiles_x(int nx) {
   return (nx + kTileCols - 1) / kTileCols;
 }
-__host__ __device__ inline int plane_tiles(int nx, int ny) {
+__host__ __device__ inline int plane_tiles(int nx, int ny,
+                                           int G = kTileRows) {
   return plane_tiles_x(nx) *
-         ((ny + kTileRows * kTileWaves - 1) / (kTileRows * kTileWaves));
+         ((ny + G * kTileWaves - 1) / (G * kTileWaves));
 }
 // Rows a disk of fixed-point radius R can cover in ny rows, and the LDS
 // bytes of K such disks (box, then chords, per disk).
@@ -119,26 +122,28 @@ __device__ __forceinline__ TileDisks tile_disks(int4 *lds, int K, int rows,
 // square is formed per row.  kTileSkip, below every such value, stays.
 constexpr int32_t kTileSkip = -1000;
 
-// The largest of the eight values.
-__device__ __forceinline__ int32_t max_of(const int32_t (&v)[kTileRows]) {
+// The largest of the values.
+template <int G>
+__device__ __forceinline__ int32_t max_of(const int32_t (&v)[G]) {
   int32_t m = v[0];
 #pragma unroll
-  for (int g = 1; g < kTileRows; ++g) m = max(m, v[g] + g * g);
+  for (int g = 1; g < G; ++g) m = max(m, v[g] + g * g);
   return m;
 }
-// At least the largest of the eight values, by less than kTileRows^2.
-__device__ __forceinline__ int32_t bound_of(const int32_t (&v)[kTileRows]) {
+// At least the largest of the values, by less than G^2.
+template <int G>
+__device__ __forceinline__ int32_t bound_of(const int32_t (&v)[G]) {
   int32_t m = v[0];
 #pragma unroll
-  for (int g = 1; g < kTileRows; ++g) m = max(m, v[g]);
-  return m + (kTileRows - 1) * (kTileRows - 1);
+  for (int g = 1; g < G; ++g) m = max(m, v[g]);
+  return m + (G - 1) * (G - 1);
 }
 // Offers a row at distance f along x, t rows from j0.
-__device__ __forceinline__ void offer_row(int32_t f, int t,
-                                          int32_t (&v)[kTileRows]) {
+template <int G>
+__device__ __forceinline__ void offer_row(int32_t f, int t, int32_t (&v)[G]) {
   int32_t c = f + t * t;
 #pragma unroll
-  for (int g = 0; g < kTileRows; ++g) {
+  for (int g = 0; g < G; ++g) {
     v[g] = min(v[g], c);
     c -= 2 * t;
   }
@@ -147,9 +152,10 @@ __device__ __forceinline__ void offer_row(int32_t f, int t,
 // Offers the chords of four rows rr, rr + dir, ... of disk k (first row z;
 // rr one of its rows) to the column's rows j0 .. j0 + 7; returns the last
 // row's distance from the column to its chord (over kNoChord / 2: none).
+template <int G>
 __device__ __forceinline__ int offer_rows(const TileDisks &d, int k, int z,
                                           int rr, int dir, int i, int j0,
-                                          int32_t (&best)[kTileRows]) {
+                                          int32_t (&best)[G]) {
   int dx[4];
   int32_t dx2[4];
 #pragma unroll
@@ -164,7 +170,7 @@ __device__ __forceinline__ int offer_rows(const TileDisks &d, int k, int z,
   int32_t c2 = dx2[2] + (t + 2 * dir) * (t + 2 * dir);
   int32_t c3 = dx2[3] + (t + 3 * dir) * (t + 3 * dir);
 #pragma unroll
-  for (int g = 0; g < kTileRows; ++g) {
+  for (int g = 0; g < G; ++g) {
     best[g] = min(min(best[g], min(c0, c1)), min(c2, c3));
     c0 -= 2 * t;
     c1 -= 2 * (t + dir);
@@ -185,12 +191,13 @@ __device__ __forceinline__ int offer_rows(const TileDisks &d, int k, int z,
 // no later row is below a value already offered.  The bounds' difference
 // over four rows, 8 dist - 16 + (dx - 1)^2 - dx_prev^2, is least for the
 // row of the tile nearest to the chord (dist rows away).
+template <int G>
 __device__ __forceinline__ void offer_disk(const TileDisks &d, int k, int i,
-                                           int j0, int32_t (&best)[kTileRows]) {
+                                           int j0, int32_t (&best)[G]) {
   const int4 b = d.box[k];
   const int z = uni(b.z), w = uni(b.w);
   const int32_t dxb2 = sq24(max(0, max(b.x - i, i - b.y)));
-  const int r0 = min(max(j0 + kTileRows / 2, z), w);
+  const int r0 = min(max(j0 + G / 2, z), w);
   auto rising = [](int dist, int dx, int prev) {
     const int m = max(dx - 1, 0);
     return dx < kNoChord / 2 && prev < kNoChord / 2 &&
@@ -204,7 +211,7 @@ __device__ __forceinline__ void offer_disk(const TileDisks &d, int k, int i,
     const int end = dir > 0 ? w : -z;
     for (int rr = dir > 0 ? r0 : r0 - 1; rr * dir <= end; rr += 4 * dir) {
       // rows between the tile and rr, and after the step's last row
-      const int gap = dir > 0 ? rr - (j0 + kTileRows - 1) : j0 - rr;
+      const int gap = dir > 0 ? rr - (j0 + G - 1) : j0 - rr;
       const int dy = max(0, gap);
       if (!any_lane(!done && bound_of(best) > dy * dy + dxb2)) break;
       const int dx = offer_rows(d, k, z, rr, dir, i, j0, best);
@@ -362,12 +369,13 @@ __device__ __forceinline__ void tile_rows_free(const TileDisks &d, int r0,
 
 // Pixels (i, j0 .. j0 + 7) of the plane P [ny][nx]; i0 is the wave's first
 // column.
+template <int G>
 __device__ __forceinline__ void plane_column(const TileDisks &d, int nx,
                                              int ny, int i0, int i, int j0,
                                              int32_t *__restrict__ P) {
-  int32_t best[kTileRows];
+  int32_t best[G];
 #pragma unroll
-  for (int g = 0; g < kTileRows; ++g)
+  for (int g = 0; g < G; ++g)
     best[g] = i < nx && j0 + g < ny ? kTileUnset : kTileSkip;
   // the disk whose box is nearest to the wave's tile first
   int kb = -1;
@@ -377,7 +385,7 @@ __device__ __forceinline__ void plane_column(const TileDisks &d, int nx,
     const int x = uni(b.x), y = uni(b.y), z = uni(b.z), w = uni(b.w);
     if (x > y || z > w) continue;
     const int dx = max(0, max(x - (i0 + kTileCols - 1), i0 - y));
-    const int dy = max(0, max(z - (j0 + kTileRows - 1), j0 - w));
+    const int dy = max(0, max(z - (j0 + G - 1), j0 - w));
     const int32_t lb = dx * dx + dy * dy;
     if (lb < near) {
       near = lb;
@@ -393,16 +401,16 @@ __device__ __forceinline__ void plane_column(const TileDisks &d, int nx,
   // pixels at distance zero are covered
   bool in = false;
 #pragma unroll
-  for (int g = 0; g < kTileRows; ++g) {
+  for (int g = 0; g < G; ++g) {
     best[g] = best[g] >= kTileFar ? kInfP : best[g] + g * g;
     in = in || best[g] == 0;
   }
   if (any_lane(in)) {
-    int32_t free2[kTileRows];  // kTileUnset only where it is needed
+    int32_t free2[G];  // kTileUnset only where it is needed
 #pragma unroll
-    for (int g = 0; g < kTileRows; ++g)
+    for (int g = 0; g < G; ++g)
       free2[g] = best[g] == 0 ? kTileUnset : kTileSkip;
-    const FreeBits bits = free_bits(d, j0 - kTileReach, i0, nx, ny);
+    const FreeBits bits = free_bits(d, j0 - tile_reach(G), i0, nx, ny);
     bool far = false;
     auto offer = [&](int r) {
       bool fr = false;
@@ -410,11 +418,11 @@ __device__ __forceinline__ void plane_column(const TileDisks &d, int nx,
       far = far || (fr && in);
       offer_row(f, r - j0, free2);
     };
-    for (int r = j0; r < min(ny, j0 + kTileRows); ++r) offer(r);
+    for (int r = j0; r < min(ny, j0 + G); ++r) offer(r);
     int q = 1;
     bool more = true;
-    for (; q < kTileReach; q += 2) {
-      const int lo = j0 - q, hi = j0 + kTileRows - 1 + q;
+    for (; q < tile_reach(G); q += 2) {
+      const int lo = j0 - q, hi = j0 + G - 1 + q;
       more = (lo >= 0 || hi < ny) && any_lane(max_of(free2) > q * q);
       if (!more) break;
       if (lo >= 0) offer(lo);
@@ -440,25 +448,25 @@ __device__ __forceinline__ void plane_column(const TileDisks &d, int nx,
         q = 1;
       }
       for (;; q += 4) {
-        const int lo = j0 - q, hi = j0 + kTileRows - 1 + q;
+        const int lo = j0 - q, hi = j0 + G - 1 + q;
         if (lo < 0 && hi >= ny) break;
         if (!any_lane(max_of(free2) > q * q)) break;
         offer8(lo - 3, hi);
       }
     }
 #pragma unroll
-    for (int g = 0; g < kTileRows; ++g)
+    for (int g = 0; g < G; ++g)
       if (best[g] == 0)
         best[g] = free2[g] >= kTileFar ? -kInfP : -(free2[g] + g * g);
   }
 #pragma unroll
-  for (int g = 0; g < kTileRows; ++g)
+  for (int g = 0; g < G; ++g)
     if (i < nx && j0 + g < ny) P[(j0 + g) * nx + i] = best[g];
 }
 
 // Tile `tile` of one slice's plane; all 64 kTileWaves lanes of the workgroup
 // (a host build's one lane loops over the pixels).
-template <class XY>
+template <int G = kTileRows, class XY>
 __device__ __forceinline__ void plane_tile(int4 *lds, int K, int rows,
                                            int64_t R, int nx, int ny,
                                            int tile, const XY &xy,
@@ -469,15 +477,15 @@ __device__ __forceinline__ void plane_tile(int4 *lds, int K, int rows,
   const int ty = tile / tx;
   const int i0 = (tile - ty * tx) * kTileCols;
 #if defined(__clang__)
-  // one lane per column and one wave per eight rows
-  const int j0 = (ty * kTileWaves + uni((int)threadIdx.x >> 6)) * kTileRows;
+  // one lane per column and one wave per G rows
+  const int j0 = (ty * kTileWaves + uni((int)threadIdx.x >> 6)) * G;
   if (j0 < ny)
-    plane_column(d, nx, ny, i0, i0 + (int)(threadIdx.x & 63), j0, P);
+    plane_column<G>(d, nx, ny, i0, i0 + (int)(threadIdx.x & 63), j0, P);
 #else
   for (int w = 0; w < kTileWaves; ++w)
     for (int c = 0; c < kTileCols; ++c)
-      if ((ty * kTileWaves + w) * kTileRows < ny)
-        plane_column(d, nx, ny, i0, i0 + c, (ty * kTileWaves + w) * kTileRows,
+      if ((ty * kTileWaves + w) * G < ny)
+        plane_column<G>(d, nx, ny, i0, i0 + c, (ty * kTileWaves + w) * G,
                      P);
 #endif
 }

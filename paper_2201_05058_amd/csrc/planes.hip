@@ -49,6 +49,14 @@ constexpr int kTileMaxRows = 2 * kTileReach;
 constexpr int kTileChords = 1664;
 constexpr int kTileChordsStack = 1024;  // where the column passes apply
 
+// Workgroups up to which a lane holds two rows of its column instead of
+// eight: such a call is over after one round of waves, whose chains of
+// dependent steps are then less than half as long.  Us a call, eight rows
+// against two: 80 x 68 x 2 slices, 4 and 8 disks 25, 34 against 19, 25 (22, 27
+// by the paths below); 147 x 104 x 2, 7 disks 28, 22; 308 x 84 x 11 (165
+// workgroups) 55, 53; but 512 x 512 x 2, 8 disks (256) 30, 35.
+constexpr int kTileFew = 192;
+
 // chords[s][k][j] = (a, b), empty when a > b.
 // Slices whose entry in `need` is zero are skipped (all slices when `need`
 // is null) by this kernel and the two below.
@@ -162,6 +170,7 @@ __global__ __launch_bounds__(kPlaneThreads) void k_planes(
 }
 
 // Tile blockIdx.x of slice blockIdx.y (+ 65535 blockIdx.z).
+template <int G>
 __global__ __launch_bounds__(64 * kTileWaves) void k_plane_tiles(
     Centres C, int K, int rows, int nx, int ny, int n_slices,
     const int32_t *__restrict__ need, int32_t *__restrict__ P) {
@@ -169,9 +178,9 @@ __global__ __launch_bounds__(64 * kTileWaves) void k_plane_tiles(
   const int s = blockIdx.z * 65535 + blockIdx.y;
   if (s >= n_slices || (need && need[s] == 0)) return;  // uniform
   const int64_t at = 2 * (int64_t)s * K;
-  plane_tile(sh4, K, rows, radius_of(C, s), nx, ny, blockIdx.x,
-             [&](int q) { return centre_word(C, at + q); },
-             P + (int64_t)s * nx * ny);
+  plane_tile<G>(sh4, K, rows, radius_of(C, s), nx, ny, blockIdx.x,
+                [&](int q) { return centre_word(C, at + q); },
+                P + (int64_t)s * nx * ny);
 }
 
 static int launch_chords(Handle *h, const Centres &C, int K, int2 *chords,
@@ -198,13 +207,18 @@ int launch_planes(Handle *h, const Centres &C, int K, bool empty,
   if (nx <= kTilePlaneMax && ny <= kTilePlaneMax && rows <= kTileMaxRows &&
       (int64_t)Keff * rows <= (stack ? kTileChordsStack : kTileChords) &&
       lds <= kTileLds) {
-    launch_timed(h, k_plane_tiles,
-                 dim3((unsigned)plane_tiles(nx, ny),
-                      (unsigned)std::min(n_slices, 65535),
-                      (unsigned)((n_slices + 65534) / 65535)),
-                 dim3(64 * kTileWaves), (uint32_t)lds, s, C, Keff, rows, nx,
-                 ny, n_slices, need, P);
-    return check_launch(h, "plane_tiles");
+    auto go = [&](auto kernel, int G) {
+      launch_timed(h, kernel,
+                   dim3((unsigned)plane_tiles(nx, ny, G),
+                        (unsigned)std::min(n_slices, 65535),
+                        (unsigned)((n_slices + 65534) / 65535)),
+                   dim3(64 * kTileWaves), (uint32_t)lds, s, C, Keff, rows, nx,
+                   ny, n_slices, need, P);
+      return check_launch(h, "plane_tiles");
+    };
+    if ((int64_t)plane_tiles(nx, ny) * n_slices <= kTileFew)
+      return go(&k_plane_tiles<2>, 2);
+    return go(&k_plane_tiles<kTileRows>, kTileRows);
   }
   int rc0 = launch_chords(h, C, Keff, chords, nx, ny, n_slices, need, s);
   if (rc0) return rc0;
