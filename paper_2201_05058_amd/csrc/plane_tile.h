@@ -13,8 +13,10 @@
 // disk, or the rest of its rows, is left out once no lane's values can still
 // fall.  Pixels covered by a chord come out as distance zero: those get the
 // distance to the nearest uncovered pixel, row by row outward, each row's
-// value again formed once per column, from bits of the row's coverage.  Both are the definition of the
-// squared distance written row by row (planes.hip), so the result is exact.
+// value again formed once per column, from bits of the row's coverage (and,
+// where a covered run is longer than the words, from its end, found once per
+// row and wave).  Both are the definition of the squared distance written
+// row by row (planes.hip), so the result is exact.
 //
 // Bound by instruction issue: about 110 vector instructions per four rows of
 // a disk and 512 pixels, and, where one round of waves covers the launch, by
@@ -223,19 +225,24 @@ __device__ __forceinline__ void offer_disk(const TileDisks &d, int k, int i,
 
 // The free pixels of 64 rows from r0 around a wave's columns, one bit each:
 // word q holds columns i0 - 64 + 64 q .. + 63 (columns outside the plane
-// are not free).  On the device lane l holds row r0 + l and at(r) reads a
-// row's words into scalar registers; a host build forms the row asked for.
+// are not free), and the distances from column i0 to the nearest free one to
+// the left of the words and to the right (kNoChord: none, or not needed, the
+// outer word having one).  On the device lane l holds row r0 + l and at(r)
+// reads a row's words into scalar registers; a host build forms the row
+// asked for.
+struct RowBits {
+  uint64_t w[3];
+  int left, right;
+};
 struct FreeBits {
 #if defined(__clang__)
-  uint64_t w[3];
+  RowBits b;
+  bool outer;  // uniform: some row has a distance beyond the words
 #else
   const TileDisks *d;
   int i0, nx, ny;
 #endif
   int r0;
-};
-struct RowBits {
-  uint64_t w[3];
 };
 // Bits a .. b of word q (bit 0 is position 64 q); none when a > b.
 __device__ __forceinline__ uint64_t bit_range(int a, int b, int q) {
@@ -256,15 +263,46 @@ __device__ __forceinline__ RowBits free_row(const TileDisks &d, int r, int i0,
     for (int q = 0; q < 3; ++q)
       f.w[q] &= ~bit_range(c.x - i0 + 64, c.y - i0 + 64, q);
   }
+  f.left = f.right = kNoChord;
   return f;
+}
+// The distances beyond the words, where an outer word has no free bit and the
+// plane goes on: the covered run's end, chord by chord.
+__device__ __forceinline__ bool free_beyond(const TileDisks &d, int r, int i0,
+                                            int nx, RowBits *f) {
+  const bool row = r >= 0;
+  const bool need_l = row && i0 > 64 && f->w[0] == 0;
+  const bool need_r = row && i0 + 128 < nx && f->w[2] == 0;
+  if (!any_lane(need_l || need_r)) return false;
+  int lo = i0 - 65, hi = i0 + 128;
+  for (bool moved = true; any_lane(moved);) {
+    moved = false;
+    for (int k = 0; k < d.K; ++k) {
+      const int4 b = d.box[k];
+      if (b.x > b.y || r < b.z || r > b.w) continue;
+      const int2 c = d.chord(k, r - b.z);
+      if (need_l && lo >= c.x && lo <= c.y) {
+        lo = c.x - 1;
+        moved = true;
+      }
+      if (need_r && hi >= c.x && hi <= c.y) {
+        hi = c.y + 1;
+        moved = true;
+      }
+    }
+  }
+  if (need_l && lo >= 0) f->left = i0 - lo;
+  if (need_r && hi < nx) f->right = hi - i0;
+  return true;
 }
 __device__ __forceinline__ FreeBits free_bits(const TileDisks &d, int r0,
                                               int i0, int nx, int ny) {
   FreeBits f;
   f.r0 = r0;
 #if defined(__clang__)
-  const RowBits b = free_row(d, r0 + (int)(threadIdx.x & 63), i0, nx, ny);
-  for (int q = 0; q < 3; ++q) f.w[q] = b.w[q];
+  const int r = r0 + (int)(threadIdx.x & 63);
+  f.b = free_row(d, r, i0, nx, ny);
+  f.outer = free_beyond(d, r, i0, nx, &f.b);
 #else
   f.d = &d;
   f.i0 = i0;
@@ -279,25 +317,31 @@ __device__ __forceinline__ RowBits bits_at(const FreeBits &f, int r) {
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
     const uint32_t lo =
-        __builtin_amdgcn_readlane((uint32_t)f.w[q], r - f.r0);
+        __builtin_amdgcn_readlane((uint32_t)f.b.w[q], r - f.r0);
     const uint32_t hi =
-        __builtin_amdgcn_readlane((uint32_t)(f.w[q] >> 32), r - f.r0);
+        __builtin_amdgcn_readlane((uint32_t)(f.b.w[q] >> 32), r - f.r0);
     b.w[q] = (uint64_t)hi << 32 | lo;
+  }
+  b.left = b.right = kNoChord;
+  if (f.outer) {
+    b.left = __builtin_amdgcn_readlane(f.b.left, r - f.r0);
+    b.right = __builtin_amdgcn_readlane(f.b.right, r - f.r0);
   }
   return b;
 #else
-  return free_row(*f.d, r, f.i0, f.nx, f.ny);
+  RowBits b = free_row(*f.d, r, f.i0, f.nx, f.ny);
+  free_beyond(*f.d, r, f.i0, f.nx, &b);
+  return b;
 #endif
 }
 // Squared distance along a row from column i0 + l (l in [0, 64)) to its
-// nearest free pixel; kTileUnset when the row has none.  *far is set when
-// the answer lies beyond the words.
-__device__ __forceinline__ int32_t row_free2(const RowBits &b, int l, int i0,
-                                             int nx, bool *far) {
-  // the side words' nearest bits are the same for all lanes; a lane's own
-  // word first (bit 0 or 63 set where it has none: the value is not used)
-  const int c0 = b.w[0] ? 1 + __builtin_clzll(b.w[0]) : kNoChord;
-  const int c2 = b.w[2] ? 64 + __builtin_ctzll(b.w[2]) : kNoChord;
+// nearest free pixel; kTileUnset when the row has none.
+__device__ __forceinline__ int32_t row_free2(const RowBits &b, int l) {
+  // the nearest bits beside the lane's word are the same for all lanes; a
+  // lane's own word first (bit 0 or 63 set where it has none: the value is
+  // not used)
+  const int c0 = b.w[0] ? 1 + __builtin_clzll(b.w[0]) : b.left;
+  const int c2 = b.w[2] ? 64 + __builtin_ctzll(b.w[2]) : b.right;
   const uint64_t le = b.w[1] & (~0ull >> (63 - l));
   const uint64_t ge = b.w[1] & (~0ull << l);
   const int own_l = l - 63 + __builtin_clzll(le | 1);
@@ -305,21 +349,15 @@ __device__ __forceinline__ int32_t row_free2(const RowBits &b, int l, int i0,
   const int dl = le ? own_l : l + c0;
   const int dr = ge ? own_r : c2 - l;
   const int m = min(dl, dr);
-  // a side without a free bit whose words end inside the plane may hide one
-  // nearer than the other side's
-  const bool far_l = dl >= kNoChord / 2, far_r = dr >= kNoChord / 2;
-  *far = (far_l & (i0 > 64) & (m > l + 64)) |
-         (far_r & (i0 + 128 < nx) & (m > 127 - l));
-  return far_l & far_r ? kTileUnset : sq24(m);
+  return m >= kNoChord / 2 ? kTileUnset : sq24(m);
 }
 
-// The same from the chords, for rows and runs of covered pixels beyond the
-// words: squared distances along eight rows from column i to each row's
-// nearest pixel that no chord covers (0: column i itself; kTileUnset: none),
-// the rows r0 + u for u < 4 and r1 + u for the others.  The covered run through i
-// grows until no chord overlaps or touches it; eight rows at a time, so that
-// their reads of the table overlap.  Rows outside the table's disks read as
-// uncovered.
+// The same from the chords, for rows beyond the lanes': squared distances
+// along eight rows from column i to each row's nearest pixel that no chord
+// covers (0: column i itself; kTileUnset: none), the rows r0 + u for u < 4
+// and r1 + u for the others.  The covered run through i grows until no chord
+// overlaps or touches it; eight rows at a time, so that their reads of the
+// table overlap.  Rows outside the table's disks read as uncovered.
 __device__ __forceinline__ void tile_rows_free(const TileDisks &d, int r0,
                                                int r1, int nx, int i, bool in,
                                                int32_t (&f)[8]) {
@@ -411,12 +449,8 @@ __device__ __forceinline__ void plane_column(const TileDisks &d, int nx,
     for (int g = 0; g < G; ++g)
       free2[g] = best[g] == 0 ? kTileUnset : kTileSkip;
     const FreeBits bits = free_bits(d, j0 - tile_reach(G), i0, nx, ny);
-    bool far = false;
     auto offer = [&](int r) {
-      bool fr = false;
-      const int32_t f = row_free2(bits_at(bits, r), i - i0, i0, nx, &fr);
-      far = far || (fr && in);
-      offer_row(f, r - j0, free2);
+      offer_row(row_free2(bits_at(bits, r), i - i0), r - j0, free2);
     };
     for (int r = j0; r < min(ny, j0 + G); ++r) offer(r);
     int q = 1;
@@ -430,8 +464,7 @@ __device__ __forceinline__ void plane_column(const TileDisks &d, int nx,
       if (lo >= 1) offer(lo - 1);
       if (hi + 1 < ny) offer(hi + 1);
     }
-    if (any_lane(far) || more) {
-      // runs longer than the words, or deeper rows: from the chords
+    if (more) {  // deeper rows: from the chords
       auto offer8 = [&](int r0, int r1) {
         int32_t f[8];
         tile_rows_free(d, r0, r1, nx, i, in, f);
@@ -442,11 +475,6 @@ __device__ __forceinline__ void plane_column(const TileDisks &d, int nx,
           offer_row(f[u], r - j0, free2);
         }
       };
-      if (any_lane(far)) {
-        // also the rows done so far
-        offer8(j0, j0 + 4);
-        q = 1;
-      }
       for (;; q += 4) {
         const int lo = j0 - q, hi = j0 + G - 1 + q;
         if (lo < 0 && hi >= ny) break;

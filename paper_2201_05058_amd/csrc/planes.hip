@@ -54,7 +54,10 @@ constexpr int kTileChordsStack = 1024;  // where the column passes apply
 // dependent steps are then less than half as long.  Us a call, eight rows
 // against two: 80 x 68 x 2 slices, 4 and 8 disks 25, 34 against 19, 25 (22, 27
 // by the paths below); 147 x 104 x 2, 7 disks 28, 22; 308 x 84 x 11 (165
-// workgroups) 55, 53; but 512 x 512 x 2, 8 disks (256) 30, 35.
+// workgroups) 55, 53; but 512 x 512 x 2, 8 disks (256) 30, 35.  In larger
+// calls on crowded planes, where most waves hold covered pixels, four rows:
+// 100 x 100, 8 disks of 42 rows, 25 and 100 slices 64, 124 against 48, 107 (53,
+// 124); 130 x 130 x 50 101, 88; elsewhere eight are as good or better.
 constexpr int kTileFew = 192;
 
 // chords[s][k][j] = (a, b), empty when a > b.
@@ -218,6 +221,9 @@ int launch_planes(Handle *h, const Centres &C, int K, bool empty,
     };
     if ((int64_t)plane_tiles(nx, ny) * n_slices <= kTileFew)
       return go(&k_plane_tiles<2>, 2);
+    // a crowd: the disks' boxes together cover two fifths of the plane
+    if (5LL * Keff * rows * rows >= 2LL * nx * ny)
+      return go(&k_plane_tiles<4>, 4);
     return go(&k_plane_tiles<kTileRows>, kTileRows);
   }
   int rc0 = launch_chords(h, C, Keff, chords, nx, ny, n_slices, need, s);
