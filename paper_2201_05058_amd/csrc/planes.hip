@@ -207,9 +207,16 @@ int launch_planes(Handle *h, const Centres &C, int K, bool empty,
   const bool stack = !need && Keff > 0 && ny <= 512 &&
                      h->tuning.static_segments == 0 &&
                      (int64_t)((nx + 63) / 64) * n_slices >= 256;
+  // such a stack of planes wider than a tile whose disks' boxes together
+  // cover them: nearly every wave holds covered pixels, many deep (100 x 100,
+  // 8 disks of 42 rows, 130, 200 and 400 slices 150, 206, 349 us a call by
+  // tiles, 140, 179, 293 by the column passes; 300 x 50 x 100, 20 of 32
+  // rows, 167, 108; but 64 x 64 x 260, 8 of 41, 101, 117)
+  const bool dense = stack && nx > kTileCols &&
+                     (int64_t)Keff * rows * rows >= (int64_t)nx * ny;
   if (nx <= kTilePlaneMax && ny <= kTilePlaneMax && rows <= kTileMaxRows &&
       (int64_t)Keff * rows <= (stack ? kTileChordsStack : kTileChords) &&
-      lds <= kTileLds) {
+      lds <= kTileLds && !dense) {
     auto go = [&](auto kernel, int G) {
       launch_timed(h, kernel,
                    dim3((unsigned)plane_tiles(nx, ny, G),

@@ -1,6 +1,7 @@
 """The planar field by tiles, with two rows of a column per lane (calls of at
-most 192 workgroups of 64 x 32 pixels) and with eight: the same planes, disks
-and crowds on either side of the line, against the oracle, exactly."""
+most 192 workgroups of 64 x 32 pixels), four (crowded planes) and eight: the
+same planes, disks and crowds on either side of the line, and stacks of planes
+so dense that they take the column passes, against the oracle, exactly."""
 import numpy as np
 import pytest
 
@@ -35,3 +36,12 @@ def test_crowds_rows_per_lane(dev, k, r, many):
     xy = 90 + rng.uniform(-50, 50, size=(n, k, 2))
     xy[0] = xy[0, :1] + np.arange(k)[:, None] * [7.0, 0.5] - [60, 0]
     check(dev, nx, ny, xy * H, r * H)
+
+
+@pytest.mark.parametrize("ny", [60, 100])
+def test_dense_stack(dev, ny):
+    # planes covered by their disks, as many as take the column passes
+    nx, n = 100, 130
+    rng = np.random.default_rng(ny)
+    xy = rng.uniform(0, 1, size=(n, 8, 2)) * [nx, ny]
+    check(dev, nx, ny, xy * H, 20.4 * H)
