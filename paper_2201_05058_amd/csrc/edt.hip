@@ -291,6 +291,9 @@ static int launch_x(Handle *h, const Occ &occ, T *out, int nx, int64_t rows,
                     hipStream_t s, const char *what) {
   if (rows <= 0) return PCSDF_OK;
   const int nch = (nx + 63) / 64;
+  if (nch > 16)  // the last kernel's chunks
+    return fail(h, PCSDF_ERR_DIMS,
+                std::string(what) + ": rows of more than 1024 voxels");
   const dim3 grid((unsigned)((rows + 3) / 4)), block(256);
   if (nch <= 1)
     launch_timed(h, k_pass_x<1, Occ, T>, grid, block, 0, s, occ, out, nx,

@@ -203,8 +203,10 @@ int launch_planes(Handle *h, const Centres &C, int K, bool empty,
   const int rows = disk_rows(max_R, ny);
   const int64_t lds = tile_lds(Keff, rows);
   // a stack with a workgroup of column segments (64 columns of a slice) per
-  // CU, in columns whose envelopes stay in LDS (16-bit entries)
-  const bool stack = !need && Keff > 0 && ny <= 512 &&
+  // CU, in columns whose envelopes stay in LDS (16-bit entries), of planes no
+  // wider than a grid: k_cover, the row pass and the entries' 10-bit roots
+  // end at 1024 columns, and a template's window may have more
+  const bool stack = !need && Keff > 0 && ny <= 512 && nx <= kMaxDim &&
                      h->tuning.static_segments == 0 &&
                      (int64_t)((nx + 63) / 64) * n_slices >= 256;
   // such a stack of planes wider than a tile whose disks' boxes together
