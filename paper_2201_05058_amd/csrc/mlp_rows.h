@@ -191,15 +191,17 @@ struct SiluFast {
 };
 // Training: the same to about one fp32 ulp.  exp(-z) = 2^t (1 + ln2 rem)
 // with t + rem = -z log2(e), t the rounded product and rem what it and the
-// constant leave out; the reciprocal gets one Newton step.  Beyond |z| = 87
-// the logistic is taken at 87, where it is 1, or 1.6e-38 (so that no
-// intermediate leaves fp32's range).
+// constant leave out; the reciprocal gets one Newton step.  So that no
+// intermediate leaves fp32's range z is taken at 87 beyond it, where the
+// logistic is 1, and at -88.5 beyond that, where its reciprocal, 3.7e-39, is
+// subnormal: the hardware's is zero there (from -87.3 on), and SiLU and its
+// derivative then are, of any finite z.
 struct SiluTrain {
   __device__ __forceinline__ static void eval(float z, float *a, float *d) {
     constexpr float kL = 1.44269504088896341f;          // log2 e, fp32
     constexpr float kLlo = 1.92596299112661746887e-8f;  // log2 e - kL
     constexpr float kLn2 = 0.693147180559945309f;
-    const float zc = __builtin_amdgcn_fmed3f(z, -87.f, 87.f);
+    const float zc = __builtin_amdgcn_fmed3f(z, -88.5f, 87.f);
     const float t = -zc * kL;
     const float e0 = __builtin_amdgcn_exp2f(t);
     const float rem = __builtin_fmaf(-zc, kLlo, __builtin_fmaf(-zc, kL, -t));
