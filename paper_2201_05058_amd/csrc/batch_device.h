@@ -27,10 +27,11 @@ struct SceneDev {
   float hf;
   uint32_t item0;   // first composite item of the scene
   uint32_t items;   // its composite items: slice groups x chunks
-  uint32_t chunks;  // voxel chunks per slice group, a multiple of eight
+  uint32_t chunks;  // voxel chunks per slice group, a multiple of 2^octet
   uint32_t span;    // slice groups per span of items
+  uint32_t octet;   // log2 of the chunks that run together, 3 or less
   FastDiv plane;    // nx ny
-  FastDiv per_span, per_oct;  // items per span, per octet of chunks in one
+  FastDiv per_span, per_oct;  // items per span, per 2^octet chunks in one
 };
 
 // Composite items are numbered scene by scene, each scene's count padded
@@ -82,6 +83,7 @@ __device__ __forceinline__ SceneDev load_scene(const SceneDev *scenes, int q) {
   d.items = c->items;
   d.chunks = c->chunks;
   d.span = c->span;
+  d.octet = c->octet;
   load_div(&d.plane, &c->plane);
   load_div(&d.per_span, &c->per_span);
   load_div(&d.per_oct, &c->per_oct);
@@ -188,9 +190,9 @@ __device__ inline void batch_planes(const SceneDev *__restrict__ scenes,
 
 // Composite item `it` belongs to scene q = scene_of[it / kItemGroup]; its
 // number within the scene, it - item0 (item0 is a multiple of eight), counts
-// spans, octets of chunks, the span's slice groups and the octet's chunks,
-// the last fastest (the order of slices_per_span's comment); it is padding
-// when it - item0 >= items.
+// spans, octets of chunks (2, 4 or one where the scene has no eight), the
+// span's slice groups and the octet's chunks, the last fastest (the order of
+// slices_per_span's comment); it is padding when it - item0 >= items.
 __device__ inline void batch_composites(const SceneDev *__restrict__ scenes,
                                         const int32_t *__restrict__ scene_of,
                                         uint32_t total, int G,
@@ -203,8 +205,10 @@ __device__ inline void batch_composites(const SceneDev *__restrict__ scenes,
     const uint32_t in_span = local - sp * sc.per_span.d;
     const uint32_t oct = quotient(in_span, sc.per_oct);
     const uint32_t in_oct = in_span - oct * sc.per_oct.d;
-    const uint32_t v0 = (oct * 8 + (in_oct & 7)) * chunk_voxels;
-    const int s0 = (int)((sp * sc.span + (in_oct >> 3)) * (uint32_t)G);
+    const uint32_t group = in_oct >> sc.octet;
+    const uint32_t v0 =
+        ((oct << sc.octet) + in_oct - (group << sc.octet)) * chunk_voxels;
+    const int s0 = (int)((sp * sc.span + group) * (uint32_t)G);
     const int s1 = min(sc.n, s0 + G);
     if (s0 >= s1 || v0 >= pack_span(sc.V, sc.aligned)) continue;
     if (sc.aligned)

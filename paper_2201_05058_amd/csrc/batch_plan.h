@@ -45,7 +45,12 @@ inline int64_t count_items(BatchPlan *bp) {
     const int64_t chunks =
         ((int64_t)pack_span(d.V, d.aligned) + bp->chunk_voxels - 1) /
         bp->chunk_voxels;
-    d.chunks = (uint32_t)((chunks + 7) / 8 * 8);
+    // eight chunks run together, one per XCD; of scenes that have fewer, all
+    // (rounded up to eight, 64 rooms of 15 x 13 x 9 x 100 slices took 140 us
+    // a batch instead of 80, 200 of 9 x 9 x 9 x 100 387 instead of 140)
+    d.octet = chunks > 4 ? 3 : chunks > 2 ? 2 : chunks > 1 ? 1 : 0;
+    const int64_t together = 1 << d.octet;
+    d.chunks = (uint32_t)((chunks + together - 1) / together * together);
     // spans of the single composite's length, whole slice groups each
     const int groups = (d.n + bp->G - 1) / bp->G;
     d.span = (uint32_t)std::max(
@@ -54,7 +59,7 @@ inline int64_t count_items(BatchPlan *bp) {
                        d.span * d.chunks;
     d.plane = fast_div((uint32_t)d.nx * (uint32_t)d.ny);
     d.per_span = fast_div(d.span * d.chunks);
-    d.per_oct = fast_div(d.span * 8);
+    d.per_oct = fast_div(d.span << d.octet);
     d.item0 = (uint32_t)next;
     d.items = (uint32_t)ct;
     next += (ct + kItemGroup - 1) / kItemGroup * kItemGroup;
