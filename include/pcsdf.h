@@ -322,7 +322,8 @@ typedef struct pcsdf_tuning {
                                          0: one, or two where only one
                                          field is written, in the order
                                          1 below */
-  int32_t batch_slices_per_item;      /* batch: slices per composite item */
+  int32_t batch_slices_per_item;      /* batch: slices per composite item;
+                                         0: by the scene, one, two or four */
   int32_t batch_chunk_quads;          /* batch: voxel quads per composite
                                          item, a multiple of 256 */
   int32_t batch_blocks_per_cu;        /* batch: persistent workgroups per CU

@@ -30,6 +30,7 @@ struct SceneDev {
   uint32_t chunks;  // voxel chunks per slice group, a multiple of 2^octet
   uint32_t span;    // slice groups per span of items
   uint32_t octet;   // log2 of the chunks that run together, 3 or less
+  int fold;         // an item holds this many times the plan's slices
   FastDiv plane;    // nx ny
   FastDiv per_span, per_oct;  // items per span, per 2^octet chunks in one
 };
@@ -84,6 +85,7 @@ __device__ __forceinline__ SceneDev load_scene(const SceneDev *scenes, int q) {
   d.chunks = c->chunks;
   d.span = c->span;
   d.octet = c->octet;
+  d.fold = c->fold;
   load_div(&d.plane, &c->plane);
   load_div(&d.per_span, &c->per_span);
   load_div(&d.per_oct, &c->per_oct);
@@ -208,8 +210,9 @@ __device__ inline void batch_composites(const SceneDev *__restrict__ scenes,
     const uint32_t group = in_oct >> sc.octet;
     const uint32_t v0 =
         ((oct << sc.octet) + in_oct - (group << sc.octet)) * chunk_voxels;
-    const int s0 = (int)((sp * sc.span + group) * (uint32_t)G);
-    const int s1 = min(sc.n, s0 + G);
+    const int slices = G * sc.fold;
+    const int s0 = (int)((sp * sc.span + group) * (uint32_t)slices);
+    const int s1 = min(sc.n, s0 + slices);
     if (s0 >= s1 || v0 >= pack_span(sc.V, sc.aligned)) continue;
     if (sc.aligned)
       composite_chunk_any<true>(sc, v0, chunk_voxels, s0, s1);

@@ -21,7 +21,7 @@ struct BatchPlan {
   std::vector<int64_t> xy;
   std::vector<size_t> xy_off;  // per scene, in int64 units
   int lds_cap = 0;
-  int G = 1;
+  int G = 1;  // slices per composite item, times the scene's fold
   uint32_t chunk_voxels = 0;
   int blocks = 0;     // persistent grid of the planar launch
   int blocks_cu = 0;  // persistent composite grid (0: one item per block)
@@ -52,9 +52,10 @@ inline int64_t count_items(BatchPlan *bp) {
     const int64_t together = 1 << d.octet;
     d.chunks = (uint32_t)((chunks + together - 1) / together * together);
     // spans of the single composite's length, whole slice groups each
-    const int groups = (d.n + bp->G - 1) / bp->G;
+    const int G = bp->G * d.fold;
+    const int groups = (d.n + G - 1) / G;
     d.span = (uint32_t)std::max(
-        1, (slices_per_span(d.V, d.n, false) + bp->G - 1) / bp->G);
+        1, (slices_per_span(d.V, d.n, false) + G - 1) / G);
     const int64_t ct = (int64_t)((groups + (int)d.span - 1) / (int)d.span) *
                        d.span * d.chunks;
     d.plane = fast_div((uint32_t)d.nx * (uint32_t)d.ny);
@@ -65,6 +66,18 @@ inline int64_t count_items(BatchPlan *bp) {
     next += (ct + kItemGroup - 1) / kItemGroup * kItemGroup;
   }
   return next;
+}
+
+// Slices per composite item where the tuning leaves them.  Both fields: one,
+// as in the single composite, but two in small scenes, whose items are over
+// before the launch has placed them all (us a batch with one and two slices:
+// 64 rooms of 16^3 x 100 slices 122, 112, 32 of 32^3 x 30 96, 89, 16 of 64^3
+// x 20 164, 160, of 80^3 272, 284).  One field: four, since a lane's address
+// and layer work bounds items of fewer (with one, two and four: 16 rooms of
+// 96^3 x 20 411, 295, 267; 4 of 240 x 240 x 128 x 20 750, 546, 518), two in
+// the smallest (200 of 9^3 x 30 79, 87, 107).
+inline int item_slices(uint32_t V, bool both) {
+  return both ? (V < 1u << 18 ? 2 : 1) : V < 1u << 13 ? 2 : 4;
 }
 
 // Validates the scenes and fills everything but device addresses.
@@ -120,6 +133,9 @@ inline int plan_batch(Handle *h, int n_scenes, const pcsdf_scene *scenes,
     d.aligned = packs_aligned((int64_t)d.nx * d.ny, (int64_t)d.V,
                               in.static_ssq_dev, in.out_ssq_dev,
                               in.out_sdf_dev);
+    d.fold = tu.batch_slices_per_item > 0
+                 ? 1
+                 : item_slices(d.V, in.out_ssq_dev && in.out_sdf_dev);
     bp->xy_off[q] = bp->xy.size();
     for (int64_t t = 0; t < (int64_t)in.n_slices * in.n_humans; ++t) {
       int64_t X, Y;
