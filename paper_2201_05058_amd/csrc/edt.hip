@@ -1172,7 +1172,8 @@ static bool plan_pays(const Handle *h, int vpl, int nx, int ny, int nz) {
     return false;
   for (int m : {ny, nz})
     if (m < 2 || m > kPropRows * kPropWaves ||
-        (m + 16) * 256 > h->max_lds)  // k_pass_col_seg's
+        (m + 16) * 256 > h->max_lds ||  // k_pass_col_seg's
+        prop_lds((m + kPropRows - 1) / kPropRows) > h->max_lds)
       return false;
   return true;
 }
@@ -1185,9 +1186,16 @@ static int launch_prop(Handle *h, const int32_t *in, int32_t *out, float *sdf,
                        hipStream_t s) {
   const int tiles = prop_tiles(nfast);
   const int waves = (m + kPropRows - 1) / kPropRows;
-  launch_timed(h, k_pass_col_prop<false, kPropRows, !kLast, kLast, kSdf>,
-               dim3((unsigned)((int64_t)tiles * nouter)), dim3(64 * waves),
-               (size_t)prop_lds(waves), s, (const void *)in, (void *)out, sdf,
+  const auto kernel = &k_pass_col_prop<false, kPropRows, !kLast, kLast, kSdf>;
+  // (more than 64 KB from 481 rows on)
+  const size_t lds = (size_t)prop_lds(waves);
+  const hipError_t e = allow_lds(reinterpret_cast<const void *>(kernel), lds);
+  if (e != hipSuccess)
+    return fail(h, PCSDF_ERR_HIP,
+                std::string("raising the LDS limit of pass_col_prop: ") +
+                    hipGetErrorString(e));
+  launch_timed(h, kernel, dim3((unsigned)((int64_t)tiles * nouter)),
+               dim3(64 * waves), lds, s, (const void *)in, (void *)out, sdf,
                hf, nfast, m, stride, outer_stride, tiles, cy, cz, bound, plan);
   return check_launch(h, "pass_col_prop");
 }
