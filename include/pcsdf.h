@@ -230,7 +230,8 @@ int pcsdf_recompute_sdf(pcsdf_handle *h, const pcsdf_grid *grid,
  * grid; otherwise an approximation of it (sub-voxel shift, the first
  * slice's voxelisation phase, unclipped windows at the grid's edge, the
  * min of separate signed fields where humans overlap).
- * Uses a workspace of 8*n_humans*(window pixels) bytes. */
+ * Uses a workspace of 8*n_humans*(window pixels) bytes.
+ * Errors: PCSDF_ERR_DIMS when a window has 2^31 - 2^20 pixels or more. */
 int pcsdf_template_composite_sdf(pcsdf_handle *h, const pcsdf_grid *grid,
                                  const int32_t *static_ssq_dev,
                                  int32_t n_slices, int32_t n_humans,

@@ -123,6 +123,13 @@ extern "C" int pcsdf_template_composite_sdf(
   const int64_t m = (R >> 16) + 2;
   const int64_t Ax = nx + m, Ay = ny + m;
   const int Wx = (int)(2 * Ax + 1), Wy = (int)(2 * Ay + 1);
+  // the planar kernels count a window's pixels, and step past their number by
+  // up to 2^19, in 32 bits
+  if (Kt >= 0 && n_humans > 0 &&
+      (int64_t)Wx * Wy > INT32_MAX - (1 << 20))
+    return fail(h, PCSDF_ERR_DIMS,
+                "template windows of " + std::to_string(Wx) + " x " +
+                    std::to_string(Wy) + " pixels: the radius is too large");
 
   // Host parameter block: window centres [K][2] int64, radii [K] int64,
   // shifts [n_slices][K] int2.
