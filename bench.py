@@ -154,6 +154,25 @@ def store_traffic(workload: str, rec: dict) -> None:
         json.dump({"records": recs}, fh, indent=1)
 
 
+# the library's rule for the 16-bit static copy (pcsdf_tuning.composite_static16)
+STATIC16_VOXELS = 1 << 26
+STATIC16_GROUPS = 24
+
+
+def composite_shape(tuning: dict, V: int, n: int):
+    """What the library launches for a composite of both fields under a
+    tuning: slices per block row, block order (single slices in the order 1
+    unless slices per block row are chosen) and whether it makes the 16-bit
+    copy of the static field."""
+    chosen = tuning.get("composite_slices_per_block") or 0
+    G = min(chosen or 1, n)
+    order = int(tuning.get("composite_order") or 0) if chosen else 1
+    c16 = tuning.get("composite_static16") or 0
+    copy16 = c16 == 2 or (c16 == 0 and V >= STATIC16_VOXELS and
+                          -(-n // G) >= STATIC16_GROUPS)
+    return G, order, copy16
+
+
 def load_traffic(workload: str, V: int, n: int, G: int, order: int):
     """Measured HBM bytes per composite call (rocprofv3 PMC FETCH_SIZE +
     WRITE_SIZE, scaled by a copy-kernel calibration) in the launch shape
@@ -386,11 +405,7 @@ def measure_workload(pc, autotune, torch, dev, sc, name: str, steps: int,
     # 16-bit static copy, k_static16 before it.
     alg_bytes = (8.0 + 4.0 / n) * V * n
     achieved = alg_bytes / comp_avg_s / 1e9
-    # the library's rule for the copy (pcsdf_tuning.composite_static16)
-    G = min(tuning.get("composite_slices_per_block") or 1, n)
-    order = int(tuning.get("composite_order") or 0)
-    c16 = tuning.get("composite_static16", 0)
-    copy16 = c16 == 2 or (c16 == 0 and V >= 1 << 25 and -(-n // G) >= 4)
+    G, order, copy16 = composite_shape(tuning, V, n)
     qy_avg = qy_ms / max(qy_n, 1)
     res = {
         "value": V * n / (ms_per_step / 1e3),

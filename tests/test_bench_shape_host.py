@@ -1,0 +1,35 @@
+"""What bench.py says of a composite's launch, against the library's rule as
+its source states it (no GPU): the 16-bit static copy's limits and the default
+shape."""
+import os
+import re
+import sys
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+sys.path.insert(0, os.path.dirname(HERE))
+
+import bench  # noqa: E402
+
+
+def test_copy_limits_are_the_librarys():
+    src = open(bench.COMPOSITE_SRC).read()
+    groups = re.search(r"kStatic16Groups = (\d+);", src)
+    voxels = re.search(r"kStatic16Voxels = 1LL << (\d+);", src)
+    g, v = int(groups.group(1)), 1 << int(voxels.group(1))
+
+    def copies(slices, tuning, vox):
+        return bench.composite_shape(tuning, vox, slices)[2]
+    assert copies(g, {}, v) and not copies(g - 1, {}, v)
+    assert not copies(g, {}, v - 1)
+    t = {"composite_slices_per_block": 3, "composite_order": 1}
+    assert copies(3 * g, t, v) and not copies(3 * g - 3, t, v)
+    assert copies(1, {"composite_static16": 2}, 1000)
+    assert not copies(2 * g, {"composite_static16": 1}, v)
+
+
+def test_launch_shape():
+    assert bench.composite_shape({}, 1000, 5)[:2] == (1, 1)
+    assert bench.composite_shape({"composite_slices_per_block": 8,
+                                  "composite_order": 0}, 1000, 5)[:2] == (5, 0)
+    assert bench.composite_shape({"composite_slices_per_block": 2,
+                                  "composite_order": 1}, 1000, 5)[:2] == (2, 1)
