@@ -57,7 +57,7 @@ def source_hash(path: str) -> str:
     with open(path) as f:
         src = f.read()
     a = src.find("// The 16-bit copy of the static field: S16[v]")
-    b = src.find("template <int VEC, bool kGather>", a)
+    b = src.find("template <bool kAligned>\nstatic void launch_comp(", a)
     text = src[a:b] if a >= 0 and b > a else src
     for dep in ("composite_device.h", "device_common.h"):
         with open(os.path.join(os.path.dirname(path), dep)) as f:

@@ -33,3 +33,25 @@ def test_launch_shape():
                                   "composite_order": 0}, 1000, 5)[:2] == (5, 0)
     assert bench.composite_shape({"composite_slices_per_block": 2,
                                   "composite_order": 1}, 1000, 5)[:2] == (2, 1)
+
+
+def test_source_hash_covers_the_kernels_alone(tmp_path):
+    """Host-side text of composite.hip leaves the hash as it is, the kernels'
+    text and the shared headers' do not."""
+    here = os.path.dirname(bench.COMPOSITE_SRC)
+    names = ("composite.hip", "composite_device.h", "device_common.h")
+    for n in names:
+        (tmp_path / n).write_text(open(os.path.join(here, n)).read())
+    path = str(tmp_path / "composite.hip")
+    h = bench.source_hash(path)
+    assert h == bench.source_hash(bench.COMPOSITE_SRC)
+    src = (tmp_path / "composite.hip").read_text()
+    (tmp_path / "composite.hip").write_text(src + "// host\n")
+    assert bench.source_hash(path) == h
+    at = src.index("__global__", src.index("k_static16("))
+    (tmp_path / "composite.hip").write_text(src[:at] + "/**/" + src[at:])
+    assert bench.source_hash(path) != h
+    (tmp_path / "composite.hip").write_text(src)
+    with open(tmp_path / "device_common.h", "a") as f:
+        f.write("// x\n")
+    assert bench.source_hash(path) != h
