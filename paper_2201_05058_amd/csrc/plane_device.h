@@ -66,7 +66,8 @@ __device__ __forceinline__ int4 disk_box(int64_t X, int64_t Y, int64_t R,
   return b;
 }
 
-// v^2 on the full-rate 24-bit multiplier: pixel offsets are below 2^11.
+// v^2 on the full-rate 24-bit multiplier: offsets are below 2^16 (2^10 within
+// a grid, more in a template's window).
 __device__ __forceinline__ int32_t sq24(int v) { return __mul24(v, v); }
 
 __device__ __forceinline__ bool covers(int2 c, int i) {
@@ -162,34 +163,14 @@ __device__ __forceinline__ int32_t scan_disk(const Tab &ch, int4 b, int k,
   return scan_rows(ch, k * ny, i, j, j0 - 1, b.z, -1, dxb2, best);
 }
 
-// Row-pass values of the free set at column i: precomputed (f1[j*nx] is
-// row j) or computed from the chords on demand.
-struct RowFreeTable {
-  const int32_t *f1;
-  int nx;
-  __device__ __forceinline__ int32_t operator()(int jr) const {
-    return f1[__mul24(jr, nx)];  // jr nx < 2^20
-  }
-};
-template <class Tab>
-struct RowFreeChords {
-  const Tab &ch;
-  int K, ny, nx, i;
-  __device__ __forceinline__ int32_t operator()(int jr) const {
-    return row_free_dist(ch, K, ny, nx, jr, i);
-  }
-};
-
 // Planar signed value of pixel (i, j): E_D outside the disk union, -E of
 // its complement inside (+-kInfP when the other set is empty).  `ch` is the
-// slice's chord table [K][ny], `box` its K boxes, rf the row pass of the
-// free set at column i.
-template <class Tab, class BoxTab, class RowFree>
-__device__ __forceinline__ int32_t plane_value_rf(const Tab &ch,
-                                                  const BoxTab &box,
-                                                  const RowFree &rf, int K,
-                                                  int nx, int ny, int i,
-                                                  int j) {
+// slice's chord table [K][ny], `box` its K boxes, f1 the row pass of the free
+// set, offset to column i.
+template <class Tab, class BoxTab>
+__device__ __forceinline__ int32_t plane_value(const Tab &ch, const BoxTab &box,
+                                               const int32_t *f1, int K,
+                                               int nx, int ny, int i, int j) {
   bool inside = false;
   for (int k = 0; k < K; ++k) inside |= covers(ch[k * ny + j], i);
   int32_t out;
@@ -217,6 +198,8 @@ __device__ __forceinline__ int32_t plane_value_rf(const Tab &ch,
   } else {
     // Rows outward from j, eight rows (four distances) per step so the
     // loads of the precomputed row distances overlap.
+    // (a row's number times nx is below 2^31, either below 2^24)
+    auto rf = [&](int jr) { return f1[__mul24(jr, nx)]; };
     int32_t best = rf(j);
     const int dmax = max(j, ny - 1 - j);
     for (int d0 = 1; d0 <= dmax; d0 += 4) {
@@ -238,14 +221,6 @@ __device__ __forceinline__ int32_t plane_value_rf(const Tab &ch,
     out = best == kInfP ? -kInfP : -best;
   }
   return out;
-}
-
-// The same with the row pass precomputed: f1 offset to column i.
-template <class Tab, class BoxTab>
-__device__ __forceinline__ int32_t plane_value(const Tab &ch, const BoxTab &box,
-                                               const int32_t *f1, int K,
-                                               int nx, int ny, int i, int j) {
-  return plane_value_rf(ch, box, RowFreeTable{f1, nx}, K, nx, ny, i, j);
 }
 
 }  // namespace pcsdf
