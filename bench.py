@@ -154,22 +154,28 @@ def store_traffic(workload: str, rec: dict) -> None:
         json.dump({"records": recs}, fh, indent=1)
 
 
-# the library's rule for the 16-bit static copy (pcsdf_tuning.composite_static16)
-STATIC16_VOXELS = 1 << 26
-STATIC16_GROUPS = 24
+# the library's rule for the 16-bit static copy of a composite of both fields
+# (pcsdf_tuning.composite_static16): grids of these sizes, with at least so
+# many slice groups up to STATIC16_FEW voxels and beyond
+STATIC16_VOXELS = 15 << 22
+STATIC16_FEW = 1 << 26
+STATIC16_MOST = 5 << 24
+STATIC16_GROUPS = (16, 4)
 
 
 def composite_shape(tuning: dict, V: int, n: int):
     """What the library launches for a composite of both fields under a
-    tuning: slices per block row, block order (single slices in the order 1
-    unless slices per block row are chosen) and whether it makes the 16-bit
-    copy of the static field."""
+    tuning: slices per block row, block order (the order 1 unless slices per
+    block row are chosen) and whether it makes the 16-bit copy of the static
+    field.  Without a chosen shape for grids of at most STATIC16_FEW voxels,
+    which take single slices."""
     chosen = tuning.get("composite_slices_per_block") or 0
     G = min(chosen or 1, n)
     order = int(tuning.get("composite_order") or 0) if chosen else 1
     c16 = tuning.get("composite_static16") or 0
-    copy16 = c16 == 2 or (c16 == 0 and V >= STATIC16_VOXELS and
-                          -(-n // G) >= STATIC16_GROUPS)
+    copy16 = c16 == 2 or (
+        c16 == 0 and STATIC16_VOXELS <= V <= STATIC16_MOST and
+        -(-n // G) >= STATIC16_GROUPS[V > STATIC16_FEW])
     return G, order, copy16
 
 

@@ -320,11 +320,11 @@ typedef struct pcsdf_scene {
  * (pcsdf_autotune_*) or set directly. */
 typedef struct pcsdf_tuning {
   int32_t composite_slices_per_block; /* composite: slices per block row;
-                                         0: one, or two where only one
-                                         field is written, in the order
-                                         1 below */
+                                         0: by the grid's size and the
+                                         fields written, in the order 1
+                                         below */
   int32_t batch_slices_per_item;      /* batch: slices per composite item;
-                                         0: by the scene, one, two or four */
+                                         0: by the scene's size and fields */
   int32_t batch_chunk_quads;          /* batch: voxel quads per composite
                                          item, a multiple of 256 */
   int32_t batch_blocks_per_cu;        /* batch: persistent workgroups per CU
@@ -351,9 +351,10 @@ typedef struct pcsdf_tuning {
                                          values beyond +-32767 are read
                                          from the field), in the handle's
                                          workspace (2 B per voxel); 0 the
-                                         copy for grids of at least 2^26
-                                         voxels with at least 24 slice
-                                         groups */
+                                         copy for grids of 15 2^22 to 5 2^24
+                                         voxels with at least 16 slice
+                                         groups (8 of one field; 4 beyond
+                                         2^26 voxels) */
 } pcsdf_tuning;
 
 int pcsdf_set_tuning(pcsdf_handle *h, const pcsdf_tuning *t);

@@ -55,7 +55,7 @@ inline int64_t count_items(BatchPlan *bp) {
     const int G = bp->G * d.fold;
     const int groups = (d.n + G - 1) / G;
     d.span = (uint32_t)std::max(
-        1, (slices_per_span(d.V, d.n, false) + G - 1) / G);
+        1, (slices_per_span(d.V, d.n) + G - 1) / G);
     const int64_t ct = (int64_t)((groups + (int)d.span - 1) / (int)d.span) *
                        d.span * d.chunks;
     d.plane = fast_div((uint32_t)d.nx * (uint32_t)d.ny);
@@ -72,12 +72,15 @@ inline int64_t count_items(BatchPlan *bp) {
 // as in the single composite, but two in small scenes, whose items are over
 // before the launch has placed them all (us a batch with one and two slices:
 // 64 rooms of 16^3 x 100 slices 122, 112, 32 of 32^3 x 30 96, 89, 16 of 64^3
-// x 20 164, 160, of 80^3 272, 284).  One field: four, since a lane's address
+// x 20 164, 160, of 80^3 272, 284), and four in scenes beyond the caches (the
+// single composite's table: 75.5 M voxels x 40 slices 6261, 4942).  One field:
+// four, since a lane's address
 // and layer work bounds items of fewer (with one, two and four: 16 rooms of
 // 96^3 x 20 411, 295, 267; 4 of 240 x 240 x 128 x 20 750, 546, 518), two in
 // the smallest (200 of 9^3 x 30 79, 87, 107).
 inline int item_slices(uint32_t V, bool both) {
-  return both ? (V < 1u << 18 ? 2 : 1) : V < 1u << 13 ? 2 : 4;
+  if (!both) return V < 1u << 13 ? 2 : 4;
+  return V < 1u << 18 ? 2 : (int64_t)V <= kSpanVoxels ? 1 : 4;
 }
 
 // Validates the scenes and fills everything but device addresses.

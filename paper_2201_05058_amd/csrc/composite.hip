@@ -304,20 +304,49 @@ int composite_run(Handle *h, const pcsdf_grid *g,
                           s, true);
 }
 
+// Grids beyond the caches.  The 256 MiB Infinity Cache holds the static field
+// up to about kLargeVoxels and its 16-bit copy up to about twice that, beside
+// the outputs that stream through it, so the best shape changes within a few
+// layers of the grid.  Kernel us (both fields; f the field, c the copy, then
+// slices per block x groups per span; the copy's own time included):
+//   voxels x slices   f1x4   c1x2   c2x1   f4x1   f6x1
+//   58.7 M x 40       2978   3050   3261   3291
+//   65.5 M x 40       3827   3514   3570   3680
+//   71.3 M x 40       4691   3799   4037   4669   4687
+//   77.6 M x 24       3797   2848   2690   3104   2861
+//   83.9 M x 30       5291   4899   4150   4394   3865
+//   105 M x 30        6637   7463   7012   5480   4803
+//   134 M x 40       12165  13021  11499   9723   9213
+//   315 M x 10        6831   7801   6885   5531   5312
+// and, with packs off the lines, 75 M x 40 c1x2 4121, c2x1 3953; 109 M x 10
+// f1x2 1974, f4x1 2383, c2x1 2565.  One field: 75.5 M x 40 f4x1 2844, c2x1
+// 2720, c4x1 2324; 105 M x 20 2104, 2835, 2552, off the lines 127 M x 30 f2x1
+// 4479, f4x1 5148.
+constexpr int64_t kCopyVoxels = 5LL << 24;  // the copy up to here
+
+// Slices per block where the tuning leaves them.  Small and middle grids: one
+// slice, in the rule's spans, or two where only one field is written (a lane's
+// address and layer work, not the stores, then bounds a block of one slice:
+// 160 x 144 x 96 x 20 slices 31 against 36 us, 255 x 241 x 127 x 20 119
+// against 153, with both fields 57 and 56, 270 and 248).
+static int block_slices(int64_t V, bool both, bool aligned, bool may_copy) {
+  if (V <= kSpanVoxels) return both ? 1 : V < kLargeVoxels ? 2 : 4;
+  if (V <= kCopyVoxels && may_copy) return both ? 2 : 4;
+  if (!aligned) return both ? 1 : 2;
+  return both ? 6 : 4;
+}
+
 // Whether the packs read the 16-bit static copy: the tuning's choice, else
-// when they read a static field of at least kStatic16Voxels voxels for at
-// least kStatic16Groups slice groups.  The copy costs 6 B per voxel once
-// (66 us at 67 M voxels) and saves 2 B per voxel and group, about 3.4 us a
-// group there: 67 M voxels x 50 slices 4.36 ms with it and 4.46 without, x
-// 10 slices 0.93 and 0.88.  At 33 M voxels the spans' re-reads already come
-// from the caches (x 40 slices 1.66 against 1.67 ms before the copy's own
-// 43 us).
-constexpr int kStatic16Groups = 24;
-constexpr int64_t kStatic16Voxels = 1LL << 26;
-static bool use_static16(const Handle *h, int64_t V, int groups) {
+// where the field exceeds the caches and the copy does not.  The copy costs 6
+// B per voxel once (66 us at 67 M voxels) and saves 2 B per voxel and slice
+// group, little where some of the field stays cached (65.5 M voxels: x 10
+// slices c1x2 961, f1x2 910; x 24 2153, 2202; one field x 20 c4x1 945, f4x1
+// 936, x 40 1766, 1930) and much beyond (73.4 M x 12 c2x1 1297, f2x1 1585).
+static bool use_static16(const Handle *h, int64_t V, int groups, bool both) {
   const int t = h->tuning.composite_static16;
-  return t == 2 ||
-         (t == 0 && V >= kStatic16Voxels && groups >= kStatic16Groups);
+  if (t != 0) return t == 2;
+  return V >= kLargeVoxels && V <= kCopyVoxels &&
+         groups >= (V > kSpanVoxels ? 4 : both ? 16 : 8);
 }
 
 int launch_composite(Handle *h, const pcsdf_grid *g,
@@ -329,23 +358,24 @@ int launch_composite(Handle *h, const pcsdf_grid *g,
   const int64_t V = (int64_t)nx * ny * nz;
   // Streaming epilogue over all voxels and slices.
   const float hf = (float)g->voxel_m;
-  // Slices per block and slice groups per span: the rule's span of blocks of
-  // one slice, or of two where only one field is written (a lane's address
-  // and layer work, not the stores, then bounds a block of one slice: 160 x
-  // 144 x 96 x 20 slices 31 against 36 us, 255 x 241 x 127 x 20 119 against
-  // 153, with both fields 57 and 56, 270 and 248); or the tuning's slices
-  // per block in spans of one group (order 0) or of the rule's slices (order
-  // 1).
+  // Slices per block and slice groups per span: the rules', or the tuning's
+  // slices per block in spans of one group (order 0) or of the rule's slices
+  // (order 1).
   const pcsdf_tuning &tu = h->tuning;
+  const bool both = out_ssq_dev && out_sdf_dev;
+  const bool aligned = packs_aligned((int64_t)nx * ny, V, static_ssq_dev,
+                                     out_ssq_dev, out_sdf_dev);
+  const bool may_copy =
+      static_copy && !need && tu.composite_static16 != 1;
   const bool chosen = tu.composite_slices_per_block > 0;
-  int G = chosen ? tu.composite_slices_per_block
-                 : (out_ssq_dev && out_sdf_dev ? 1 : 2);
-  G = std::min(G, n_slices);
+  const int G = std::min(chosen ? tu.composite_slices_per_block
+                                : block_slices(V, both, aligned, may_copy),
+                         n_slices);
   const int groups = (n_slices + G - 1) / G;
-  const bool copy16 = static_copy && !need && use_static16(h, V, groups);
+  const bool copy16 = may_copy && use_static16(h, V, groups, both);
   int span = 1;
   if (!chosen || tu.composite_order == 1)
-    span = std::max(1, (slices_per_span(V, n_slices, copy16) + G - 1) / G);
+    span = std::max(1, (slices_per_span(V, n_slices) + G - 1) / G);
   // gridDim.z, which also holds up to 3 parts of the octets
   while ((groups + span - 1) / span > 65535 / 3) ++span;
   const uint32_t plane = (uint32_t)nx * (uint32_t)ny;
@@ -362,8 +392,7 @@ int launch_composite(Handle *h, const pcsdf_grid *g,
     if ((rc = check_launch(h, "static16"))) return rc;
     S16 = c;
   }
-  if (packs_aligned((int64_t)nx * ny, V, static_ssq_dev, out_ssq_dev,
-                    out_sdf_dev))
+  if (aligned)
     launch_comp<true>(h, static_ssq_dev, P, need, out_ssq_dev, out_sdf_dev,
                       plane, n_slices, G, span, Kt, has_above, hf, Vu, S16, s);
   else

@@ -131,17 +131,22 @@ __host__ __device__ inline uint32_t pack_span(uint32_t V, bool aligned) {
 //    6.5 TB/s (all slices in one span 6.0), 6.3 M 6.4 (6.1);
 //  - larger fields do not: 8.4 M voxels run one slice at a time at 4.9
 //    TB/s, in spans of 10 at 6.3; 16.8 M 4.9 and 6.3;
-//  - from 2^25 voxels the outputs of a long span compete (a slice is 128 MB
-//    or more apart): 33 M voxels x 40 slices spans of 4 6.4 TB/s, of 10 6.1,
-//    of 40 5.3; from 2^26, with the 16-bit copy, 67 M x 50 spans of 2 6.25,
-//    of 10 5.6, of 50 5.1.
+//  - from 15 2^21 voxels the outputs of a long span compete (a slice is 120
+//    MB or more apart): 33 M voxels x 40 slices spans of 4 6.4 TB/s, of 10
+//    6.1, of 40 5.3; 31.5 M x 20 784 us and 820, 512 x 512 x 127 x 40 1945
+//    and 2208;
+//  - from kLargeVoxels on, where the static field alone fills the Infinity
+//    Cache, 67 M x 50 with the 16-bit copy spans of 2 6.25, of 10 5.6, of 50
+//    5.1; up to four slices are still one span (67 M x 3 278 us, 338 in two).
 // A span is at most n and spans of one grid are about equally long.
-__host__ __device__ inline int slices_per_span(int64_t V, int n,
-                                               bool copy16) {
-  const int most = V <= (3LL << 21) ? 1
-                   : V < (1LL << 25) ? 10
-                   : V < (1LL << 26) || !copy16 ? 4
-                                                : 2;
+constexpr int64_t kLargeVoxels = 15LL << 22;  // 240 MiB of the 256
+constexpr int64_t kSpanVoxels = 1LL << 26;    // single slices up to here
+__host__ __device__ inline int slices_per_span(int64_t V, int n) {
+  const int most = V <= (3LL << 21)   ? 1
+                   : V < (15LL << 21) ? 10
+                   : V < kLargeVoxels ? 4
+                   : n <= 4           ? n
+                                      : 2;
   const int spans = (n + most - 1) / most;
   return (n + spans - 1) / spans;
 }

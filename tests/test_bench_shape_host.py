@@ -11,20 +11,32 @@ sys.path.insert(0, os.path.dirname(HERE))
 import bench  # noqa: E402
 
 
+def library_constant(path, name):
+    with open(path) as f:
+        m = re.search(name + r" = (\d+)LL << (\d+);", f.read())
+    return int(m.group(1)) << int(m.group(2))
+
+
 def test_copy_limits_are_the_librarys():
-    src = open(bench.COMPOSITE_SRC).read()
-    groups = re.search(r"kStatic16Groups = (\d+);", src)
-    voxels = re.search(r"kStatic16Voxels = 1LL << (\d+);", src)
-    g, v = int(groups.group(1)), 1 << int(voxels.group(1))
+    src = bench.COMPOSITE_SRC
+    dev = os.path.join(os.path.dirname(src), "composite_device.h")
+    low = library_constant(dev, "kLargeVoxels")
+    mid = library_constant(dev, "kSpanVoxels")
+    most = library_constant(src, "kCopyVoxels")
+    with open(src) as f:
+        m = re.search(r"groups >= \(V > kSpanVoxels \? (\d+) : both \? (\d+)",
+                      f.read())
+    few, many = int(m.group(1)), int(m.group(2))
 
     def copies(slices, tuning, vox):
         return bench.composite_shape(tuning, vox, slices)[2]
-    assert copies(g, {}, v) and not copies(g - 1, {}, v)
-    assert not copies(g, {}, v - 1)
-    t = {"composite_slices_per_block": 3, "composite_order": 1}
-    assert copies(3 * g, t, v) and not copies(3 * g - 3, t, v)
+    for v, g in [(low, many), (mid, many), (mid + 1, few), (most, few)]:
+        assert copies(g, {}, v) and not copies(g - 1, {}, v)
+        t = {"composite_slices_per_block": 3, "composite_order": 1}
+        assert copies(3 * g, t, v) and not copies(3 * g - 3, t, v)
+    assert not copies(many, {}, low - 1) and not copies(many, {}, most + 1)
     assert copies(1, {"composite_static16": 2}, 1000)
-    assert not copies(2 * g, {"composite_static16": 1}, v)
+    assert not copies(2 * many, {"composite_static16": 1}, mid)
 
 
 def test_launch_shape():
