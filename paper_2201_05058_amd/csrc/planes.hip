@@ -44,7 +44,16 @@ namespace pcsdf {
 //   360, 774 per pixel;  512 x 512 x 2: 8, 32, 64 disks 30, 50, 505 against
 //   36, 82, 164.
 // The lines are drawn in chords per slice, disks times rows.
+// Crowds on small planes are the same when their discs are large for the
+// plane: covered pixels then lie deeper than the words' rows.  The depth goes
+// with how often the boxes cover the plane, times the rows of a disk: above
+// kTileDepth tiles lose (us a call, tiles and the path below: 64 x 64 x 12, 8
+// disks of 41 rows, 134, 82, 37; 100 x 100 x 12, 16 of 41, 110, 229, 59; 128 x
+// 96 x 12, 8 of 51, 86, 48, 40; 48 x 64 x 12, 16 of 25, 81, 69, 51), under it
+// they win (64 x 100 x 12, 32 of 25, 78, 53, 74; 48 x 64 x 12, 8 of 31, 77, 29,
+// 34; 140 x 140 x 12, 16 of 41, 56, 52, 59; 48 x 64 x 12, 40 of 17, 64, 58, 80).
 constexpr int64_t kTileLds = 48 * 1024;
+constexpr int64_t kTileDepth = 80;
 constexpr int kTileMaxRows = 2 * kTileReach;
 constexpr int kTileChords = 1664;
 constexpr int kTileChordsStack = 1024;  // where the column passes apply
@@ -216,9 +225,11 @@ int launch_planes(Handle *h, const Centres &C, int K, bool empty,
   // rows, 167, 108; but 64 x 64 x 260, 8 of 41, 101, 117)
   const bool dense = stack && nx > kTileCols &&
                      (int64_t)Keff * rows * rows >= (int64_t)nx * ny;
+  const bool deep =
+      (int64_t)Keff * rows * rows * rows >= kTileDepth * nx * ny;
   if (nx <= kTilePlaneMax && ny <= kTilePlaneMax && rows <= kTileMaxRows &&
       (int64_t)Keff * rows <= (stack ? kTileChordsStack : kTileChords) &&
-      lds <= kTileLds && !dense) {
+      lds <= kTileLds && !dense && !deep) {
     auto go = [&](auto kernel, int G) {
       launch_timed(h, kernel,
                    dim3((unsigned)plane_tiles(nx, ny, G),
