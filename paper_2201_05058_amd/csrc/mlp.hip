@@ -125,11 +125,12 @@ static int check_rows(Mlp *m, int n, const void *x) {
 // [0, min(n, *n_dev)) read on the device).
 static int mlp_infer(Mlp *m, int n, const int *n_dev, const float *x,
                      float *y, float *gx, hipStream_t s) {
-  const int tiles = (n + kRowTile - 1) / kRowTile;
-  const int grid = std::min(tiles, kInferBlocks);
-  if (grid == 0) return PCSDF_OK;
-  hipLaunchKernelGGL(k_mlp_infer, dim3(grid), dim3(64 * kRowWaves), 0, s, x,
-                     n, n_dev, m->n_in,
+  if (n == 0) return PCSDF_OK;
+  const bool few = n <= kFewRows;
+  const int rows = few ? 32 : kRowTile;
+  const int grid = std::min((n + rows - 1) / rows, kInferBlocks);
+  hipLaunchKernelGGL(few ? k_mlp_infer_few : k_mlp_infer, dim3(grid),
+                     dim3(64 * kRowWaves), 0, s, x, n, n_dev, m->n_in,
                      reinterpret_cast<const float *>(m->norm.ptr), weights(m),
                      pf(m), m->out_scale, y, gx);
   return check_launch(m->h, "mlp inference");
