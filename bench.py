@@ -155,8 +155,11 @@ def store_traffic(workload: str, rec: dict) -> None:
 
 
 # the library's rule for the 16-bit static copy of a composite of both fields
-# (pcsdf_tuning.composite_static16): grids of these sizes, with at least so
-# many slice groups up to STATIC16_FEW voxels and beyond
+# (pcsdf_tuning.composite_static16): grids of STATIC16_VOXELS to STATIC16_MOST
+# with at least so many slice groups up to STATIC16_FEW voxels and beyond, or,
+# with groups apart (order 0 chosen), the second number; single slices apart
+# from STATIC16_SINGLE on
+STATIC16_SINGLE = 1 << 25
 STATIC16_VOXELS = 15 << 22
 STATIC16_FEW = 1 << 26
 STATIC16_MOST = 5 << 24
@@ -173,9 +176,10 @@ def composite_shape(tuning: dict, V: int, n: int):
     G = min(chosen or 1, n)
     order = int(tuning.get("composite_order") or 0) if chosen else 1
     c16 = tuning.get("composite_static16") or 0
+    least = STATIC16_SINGLE if order == 0 and G == 1 else STATIC16_VOXELS
     copy16 = c16 == 2 or (
-        c16 == 0 and STATIC16_VOXELS <= V <= STATIC16_MOST and
-        -(-n // G) >= STATIC16_GROUPS[V > STATIC16_FEW])
+        c16 == 0 and least <= V <= STATIC16_MOST and
+        -(-n // G) >= STATIC16_GROUPS[order == 0 or V > STATIC16_FEW])
     return G, order, copy16
 
 

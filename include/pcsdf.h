@@ -354,7 +354,9 @@ typedef struct pcsdf_tuning {
                                          copy for grids of 15 2^22 to 5 2^24
                                          voxels with at least 16 slice
                                          groups (8 of one field; 4 beyond
-                                         2^26 voxels) */
+                                         2^26 voxels, and in the order 0
+                                         chosen, there from 2^25 voxels on
+                                         with single slices) */
 } pcsdf_tuning;
 
 int pcsdf_set_tuning(pcsdf_handle *h, const pcsdf_tuning *t);

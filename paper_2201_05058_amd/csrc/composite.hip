@@ -342,11 +342,18 @@ static int block_slices(int64_t V, bool both, bool aligned, bool may_copy) {
 // group, little where some of the field stays cached (65.5 M voxels: x 10
 // slices c1x2 961, f1x2 910; x 24 2153, 2202; one field x 20 c4x1 945, f4x1
 // 936, x 40 1766, 1930) and much beyond (73.4 M x 12 c2x1 1297, f2x1 1585).
-static bool use_static16(const Handle *h, int64_t V, int groups, bool both) {
-  const int t = h->tuning.composite_static16;
-  if (t != 0) return t == 2;
-  return V >= kLargeVoxels && V <= kCopyVoxels &&
-         groups >= (V > kSpanVoxels ? 4 : both ? 16 : 8);
+// Where the tuning has the groups apart (order 0) nothing of the field stays
+// cached between them (65.5 M x 40, three slices 3585, 3758), and single
+// slices read it that often from 2^25 voxels on (50 M x 40 2851, 3307).
+static bool use_static16(const Handle *h, int64_t V, int G, int groups,
+                         bool both) {
+  const pcsdf_tuning &tu = h->tuning;
+  if (tu.composite_static16 != 0) return tu.composite_static16 == 2;
+  const bool apart =
+      tu.composite_slices_per_block > 0 && tu.composite_order == 0;
+  const int64_t least = apart && G == 1 ? 1LL << 25 : kLargeVoxels;
+  return V >= least && V <= kCopyVoxels &&
+         groups >= (apart || V > kSpanVoxels ? 4 : both ? 16 : 8);
 }
 
 int launch_composite(Handle *h, const pcsdf_grid *g,
@@ -372,7 +379,7 @@ int launch_composite(Handle *h, const pcsdf_grid *g,
                                 : block_slices(V, both, aligned, may_copy),
                          n_slices);
   const int groups = (n_slices + G - 1) / G;
-  const bool copy16 = may_copy && use_static16(h, V, groups, both);
+  const bool copy16 = may_copy && use_static16(h, V, G, groups, both);
   int span = 1;
   if (!chosen || tu.composite_order == 1)
     span = std::max(1, (slices_per_span(V, n_slices) + G - 1) / G);

@@ -24,7 +24,8 @@ def test_copy_limits_are_the_librarys():
     mid = library_constant(dev, "kSpanVoxels")
     most = library_constant(src, "kCopyVoxels")
     with open(src) as f:
-        m = re.search(r"groups >= \(V > kSpanVoxels \? (\d+) : both \? (\d+)",
+        m = re.search(r"groups >= \(apart \|\| V > kSpanVoxels \? (\d+)"
+                      r" : both \? (\d+)",
                       f.read())
     few, many = int(m.group(1)), int(m.group(2))
 
@@ -34,6 +35,12 @@ def test_copy_limits_are_the_librarys():
         assert copies(g, {}, v) and not copies(g - 1, {}, v)
         t = {"composite_slices_per_block": 3, "composite_order": 1}
         assert copies(3 * g, t, v) and not copies(3 * g - 3, t, v)
+    for g3, v3 in [(3, low), (3, mid), (1, low), (1, 1 << 25)]:
+        t = {"composite_slices_per_block": g3, "composite_order": 0}
+        assert copies(g3 * few, t, v3) and not copies(g3 * (few - 1), t, v3)
+        assert not copies(99, t, v3 - 1) or g3 == 1 or v3 == mid
+    t = {"composite_slices_per_block": 1, "composite_order": 0}
+    assert not copies(99, t, (1 << 25) - 1)
     assert not copies(many, {}, low - 1) and not copies(many, {}, most + 1)
     assert copies(1, {"composite_static16": 2}, 1000)
     assert not copies(2 * many, {"composite_static16": 1}, mid)
