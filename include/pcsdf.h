@@ -420,7 +420,7 @@ int pcsdf_autotune_composite(pcsdf_handle *h, const pcsdf_scene *scene,
  * W0[128][n_in] b0[128] W1[128][128] b1 W2[128][128] b2 W3[128][128] b3
  * W4[1][128] b4[1].  The network object owns its weights, optimiser state
  * and workspace on the handle's device; calls on one network must not
- * overlap.  Training batches are padded internally to a multiple of 1024
+ * overlap.  Training batches are padded internally to a multiple of 128
  * rows. */
 #define PCSDF_MLP_MAX_IN 32
 #define PCSDF_SURROGATE_IN 16 /* features per (query, human) row */

@@ -120,7 +120,7 @@ using namespace pcsdf;
 // The batch captured twice, each with an upload from its own pinned copy of
 // the parameters: new positions go into the copy that the last launch does
 // not read, so that they are set, and the next launch is queued, while that
-// one runs (8 rooms, 1 ms of kernels: 77 us between launches otherwise).  The
+// one runs (16 rooms, 1 ms of kernels: 77 us between launches otherwise).  The
 // device's parameters and scratch are one; launches are ordered.
 struct pcsdf_batch_graph {
   struct Copy {

@@ -95,6 +95,12 @@ __device__ __forceinline__ SceneDev load_scene(const SceneDev *scenes, int q) {
 constexpr int kItemPlane = 0;
 
 // Whether a scene's planar items are tiles with the slice's disks in LDS.
+// The single call's limits on rows and chords (planes.hip) do not apply: what
+// it falls back to is not at hand here, and beside the items of one pixel per
+// lane with the chords in LDS, or of a whole slice without, tiles win at any
+// disks.  Us a batch of 16 rooms of about 200 x 200 x 64 x 20 slices, those
+// items and tiles: 8 disks of 81 rows 10990, 1802, 4 of 201 rows 14238, 3329,
+// 26 of 41 22767, 1598, 128 of 27 28276, 2988; 1 of 61 1174, 1087.
 __host__ __device__ inline bool planes_tiled(int K, int64_t R, int ny,
                                              int lds_cap) {
   return tile_lds(K, disk_rows(R, ny)) <= lds_cap;

@@ -1152,7 +1152,9 @@ int launch_pass_col(Handle *h, const int32_t *in, int32_t *out,
 // one in which it is not pays about 18 us for k_reach and the launches that
 // return at once, and gets back what the 16-bit distances save the x and y
 // passes: 376 -> 381 us at 34 M voxels, 515 -> 521 at 41 M, 602 -> 603 at
-// 51 M, 1018 -> 995 at 67 M.  The line is where that is even.
+// 51 M, 1018 -> 995 at 67 M.  The line is the least size at which no map
+// loses, not the best one over all maps: below it near maps give up what they
+// would gain (240 us at 34 M) so that the others do not lose 5 us.
 constexpr int64_t kPlanVoxels = 3LL << 24;
 
 // Blocks along an axis of n voxels; 128-column tiles of nx.

@@ -22,9 +22,9 @@ constexpr int kPartLen = kPartW4 + kHid + 4;
 
 // A layer's activations or gradients in memory: per 32 rows the KS
 // fragments of the wave that holds them, 1 KB each, so that a wave stores
-// and a slab is copied in whole cache lines (with row-major stores, 32
-// bytes per row and instruction, the row kernel took 52 us instead of 49
-// at 65,536 rows).  Element (row r of the 32, unit u) of such a block:
+// and a slab is copied in whole cache lines (row-major stores, 32 bytes per
+// row and instruction, cost the row kernel 3 us more at 65,536 rows).
+// Element (row r of the 32, unit u) of such a block:
 __device__ __forceinline__ int block_at(int r, int u) {
   return ((u >> 4) * 64 + r + 32 * ((u >> 3) & 1)) * 8 + (u & 7);
 }
@@ -43,13 +43,16 @@ __device__ __forceinline__ void store_frags(uint16_t *__restrict__ dst,
 // is given; sbuf[m] = seed * out_scale; lpart[wave] = the wave's sum of
 // squared residuals.  act and dz hold 4 layers of `stride` elements.
 //
-// Bound by vector instructions: per 64 values of a layer the SiLU pair is
-// 15 of them and two transcendentals (about 90 cycles) against 26 matrix
-// cycles forward and back.  222 registers hold the four layers'
-// derivatives (128), the accumulators (64) and one layer's fragments: two
-// waves per SIMD, whose matrix and vector phases overlap.  65,536 rows of 16
-// inputs: 42 us (480 TFLOP/s); the layer-by-layer kernels this replaces,
-// with activations in memory between them, took 135 us for the same work.
+// Bound by vector instructions and, as much again, by waits that two waves
+// per SIMD do not cover: per 64 values of a layer the SiLU pair is 15
+// instructions and two transcendentals (about 90 cycles) against 26 matrix
+// cycles forward and back; of 41 us for 65,536 rows of 16 inputs (490
+// TFLOP/s) a SIMD issues vector instructions for 19 and runs the matrix unit
+// for 5, and 28 % of the waves' cycles wait for a layer's weights or for the
+// barriers around them.  222 registers hold the four layers' derivatives
+// (128), the accumulators (64) and one layer's fragments.  The
+// layer-by-layer kernels this replaces, with activations in memory between
+// them, took 135 us for the same work.
 __global__ __launch_bounds__(64 * kRowWaves, 2) void k_mlp_train_rows(
     const float *__restrict__ x, int n, int n_in,
     const float *__restrict__ norm, NetWeights w, const float *__restrict__ p,

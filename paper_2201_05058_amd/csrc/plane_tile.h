@@ -18,12 +18,14 @@
 // row and wave).  Both are the definition of the squared distance written
 // row by row (planes.hip), so the result is exact.
 //
-// Bound by instruction issue: about 110 vector instructions per four rows of
-// a disk and 512 pixels, and, where one round of waves covers the launch, by
-// the waves that hold covered pixels (about 25 rows of 75 instructions
-// more).  Planar fields of a call: 256 x 256 x 20 slices x 3 discs 19 us in
+// Bound by instruction issue (512 x 512 x 50 x 8 issues in about every cycle of
+// its SIMDs, three vector to two scalar instructions): about 110 vector
+// instructions per four rows of a disk and 512 pixels; where one round of
+// waves covers the launch, by the waves that hold covered pixels (about 25
+// rows of 75 instructions more), which wait half their cycles on the chords'
+// table.  Planar fields of a call: 256 x 256 x 20 slices x 3 discs 19 us in
 // one launch (chords, row pass and one pixel per lane: 40 us in three), 512
-// x 512 x 50 x 8 131-180 us (265 by coverage and column passes beside the
+// x 512 x 50 x 8 128-141 us (265 by coverage and column passes beside the
 // other kernels of the call), 16 uneven rooms of a batch 57 us (326).
 #pragma once
 
