@@ -26,8 +26,7 @@ struct SceneDev {
   int aligned;  // every composite pack is aligned (packs_aligned)
   float hf;
   uint32_t item0;   // first composite item of the scene
-  uint32_t items;   // its composite items: slice groups x chunks
-  uint32_t chunks;  // voxel chunks per slice group, a multiple of 2^octet
+  uint32_t items;   // its composite items: slice groups x voxel chunks
   uint32_t span;    // slice groups per span of items
   uint32_t octet;   // log2 of the chunks that run together, 3 or less
   int fold;         // an item holds this many times the plan's slices
@@ -82,7 +81,6 @@ __device__ __forceinline__ SceneDev load_scene(const SceneDev *scenes, int q) {
   d.hf = c->hf;
   d.item0 = c->item0;
   d.items = c->items;
-  d.chunks = c->chunks;
   d.span = c->span;
   d.octet = c->octet;
   d.fold = c->fold;

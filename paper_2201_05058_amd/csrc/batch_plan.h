@@ -42,24 +42,23 @@ inline bool fixed(double p, double o, double h, int64_t *out) {
 inline int64_t count_items(BatchPlan *bp) {
   int64_t next = 0;
   for (SceneDev &d : bp->scenes) {
-    const int64_t chunks =
+    uint32_t chunks = (uint32_t)(
         ((int64_t)pack_span(d.V, d.aligned) + bp->chunk_voxels - 1) /
-        bp->chunk_voxels;
+        bp->chunk_voxels);
     // eight chunks run together, one per XCD; of scenes that have fewer, all
     // (rounded up to eight, 64 rooms of 15 x 13 x 9 x 100 slices took 140 us
     // a batch instead of 80, 200 of 9 x 9 x 9 x 100 387 instead of 140)
     d.octet = chunks > 4 ? 3 : chunks > 2 ? 2 : chunks > 1 ? 1 : 0;
-    const int64_t together = 1 << d.octet;
-    d.chunks = (uint32_t)((chunks + together - 1) / together * together);
+    chunks = (((chunks - 1) >> d.octet) + 1) << d.octet;
     // spans of the single composite's length, whole slice groups each
     const int G = bp->G * d.fold;
     const int groups = (d.n + G - 1) / G;
     d.span = (uint32_t)std::max(
         1, (slices_per_span(d.V, d.n) + G - 1) / G);
     const int64_t ct = (int64_t)((groups + (int)d.span - 1) / (int)d.span) *
-                       d.span * d.chunks;
+                       d.span * chunks;
     d.plane = fast_div((uint32_t)d.nx * (uint32_t)d.ny);
-    d.per_span = fast_div(d.span * d.chunks);
+    d.per_span = fast_div(d.span * chunks);
     d.per_oct = fast_div(d.span << d.octet);
     d.item0 = (uint32_t)next;
     d.items = (uint32_t)ct;
