@@ -67,7 +67,8 @@ def source_hash(path: str) -> str:
 
 def composite_outputs(torch, n, shape_zyx, dev):
     """The composite calls' default output layout (the package's
-    composite_outputs: both fields in one allocation, 4 KiB apart)."""
+    composite_outputs: both fields in one allocation, the fp32 one on the
+    first line 4 KiB past the other)."""
     import paper_2201_05058_amd as pc
     return pc.composite_outputs(n, shape_zyx, dev)
 
